@@ -105,11 +105,9 @@ typedef enum rrf_stage {
  *   dtype        RRF_F32 or RRF_F64.
  *   m_max,n_max  largest A the plan will see (>= 1).
  *   block_b_max  largest block size b, 1 <= block_b_max <= 128.  A block runs
- *                as sub-blocks of at most 64 columns (32 on matrices of at
- *                most 512 MiB, where a narrow update beside a narrow panel
- *                is faster; the last one ragged): Householder QR is column
- *                by column, so the reflectors are the block's own; the stop
- *                test runs once per block.
+ *                as sub-blocks of at most 64 columns (the last one ragged):
+ *                Householder QR is column by column, so the reflectors are
+ *                the block's own; the stop test runs once per block.
  *   k_max        rank cap (>= 0); 0 means min(m, n).  A cap below the rank the
  *                tolerance needs is the fixed-rank mode of Sec. 6 (Fig. 6).
  *   hip_stream   hipStream_t to enqueue on; NULL means the null stream.
@@ -118,8 +116,8 @@ typedef enum rrf_stage {
  *                larger than the device holds at once; work on other streams
  *                that occupies the device delays them (their waits are
  *                bounded: RRF_ERR_INTERNAL if one runs out).
- * Panels taller than the register-resident panel grid holds (65536 rows for
- * 64 columns, 131072 for 32, 262144 for 16 on 256 CUs) are factored by a
+ * Panels taller than the register-resident panel grid holds (131072 rows
+ * for 64 columns, 262144 for 32, 524288 for 16 on 256 CUs) are factored by a
  * tall-skinny QR tree instead (no look-ahead for them).
  * Returns RRF_ERR_SHAPE if m_max exceeds even that tree (about 4 million rows
  * at 64 columns), RRF_ERR_HIP if there is no usable GPU, RRF_ERR_NOMEM on

@@ -38,8 +38,9 @@ constexpr int kOmLd = 256;        // Omega stored [c][q]: a batch of 256 sketch 
 constexpr int kPanelGrid = 0;      // column-by-column panel, one grid reduction per column
 constexpr int kPanelTsqr = 1;      // tall-skinny QR + Householder reconstruction
 constexpr int kPanelGram = 2;      // column recurrence from the Gram matrix, one exchange per sweep
-constexpr int kPanelAuto = 3;      // kPanelGram for blocks of <= 32 columns, else kPanelGrid
+constexpr int kPanelAuto = 3;      // kPanelGram
 constexpr int kTLd = 64;          // T stored like geqrt's T: 64 rows
+constexpr double kLookaheadBytes = 512.0 * (1 << 20);   // largest matrix with look-ahead
 
 struct Sizes {
   int64_t ldb, kcap, kcols;
@@ -73,7 +74,7 @@ Sizes compute_sizes(rrf_dtype dt, int64_t m_max, int64_t n_max, int64_t b_max,
   z.Tm = (size_t)kTLd * z.kcols * 8;
   z.tau = (size_t)z.kcols * 8;
   z.Ypart = (size_t)kMaxUpdSplits * z.ldb * 64 * e;
-  z.ldysum = z.ldb + 1024;   // >= the panel grid's padded row count
+  z.ldysum = z.ldb + 2048;   // >= the panel grid's padded row count
   z.Ysum = (size_t)z.ldysum * 64 * 8;
   // Omega and W carry zero rows up to the next multiple of the update chunk.
   z.Om = (size_t)(n_max + kUpdChunk) * kOmLd * e;
@@ -152,7 +153,7 @@ struct rrf_plan {
   int stop_mode, timing, panel_target;
   int log;                   // RRF_LOG=1: one stderr line per run, one per block
   int gram_fused_max;         // most workgroups of a Gram panel inside the update's launch
-  int sub_max;                // widest sub-block (16, 32 or 64 columns; 0: by size)
+  int sub_max;                // widest sub-block (16, 32 or 64 columns; 0: 64)
   unsigned spin_limit;       // poll rounds of a grid-wide wait (run state)
   unsigned panel_launches;   // epochs of the panel's tagged partials
   // last run
@@ -363,13 +364,10 @@ hipError_t read_state(rrf_plan* p) {
   return hipStreamSynchronize(p->stream);
 }
 
-// The panel algorithm for a block of b columns.  Narrow panels take the Gram
-// form (its column steps are cheap at 32 columns and it exchanges once per
-// sweep); 64-column panels take the column-by-column grid.  The look-ahead
-// hides either inside the update.
-int panel_alg(const rrf_plan* p, int64_t b) {
-  if (p->panel_mode != kPanelAuto) return p->panel_mode;
-  return pad16(b) <= 32 ? kPanelGram : kPanelGrid;
+// The panel algorithm: the Gram form (one grid exchange per sweep of columns)
+// unless the plan forces another.
+int panel_alg(const rrf_plan* p) {
+  return p->panel_mode != kPanelAuto ? p->panel_mode : kPanelGram;
 }
 
 // The route an m x b panel takes: the plan's algorithm when its
@@ -378,7 +376,7 @@ int panel_alg(const rrf_plan* p, int64_t b) {
 // no route fits (beyond the tree's depth).  sh->rows_pad is the row count
 // the gathered panel must cover.
 int panel_route(const rrf_plan* p, int64_t m, int b, PanelShape* sh) {
-  const int alg = panel_alg(p, b);
+  const int alg = panel_alg(p);
   if (alg == kPanelGram && gram_panel_shape(m, b, p->num_cus, sh)) return kPanelGram;
   if (alg == kPanelGrid && panel_shape(m, b, p->num_cus, p->panel_target, sh)) return kPanelGrid;
   TsqrShape ts;
@@ -525,23 +523,8 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   // updated B gives the block's reflectors (Q_1^T (B Omega_2) =
   // (Q_1^T B) Omega_2).  The stop test runs at the end of each block only.
   //
-  // The sub-block width: 64 columns, or 32 when the matrix is small (at most
-  // 512 MiB).  There a 64-column update is short beside the 64-column panel
-  // factored inside its launch (4096 x 11008 fp32: about 100 us against
-  // 300 us), while 32-column sub-blocks put a Gram panel of about the
-  // update's length beside each update (15.1 -> 12.7 ms per run there; at
-  // 16384 x 16384 fp64 64 columns stay faster, 33.5 against 45.6 ms).
-  // The spectral stop test estimates from the next block's first min(b, 64)
-  // sketch columns, the sample of a 64-column sub-block.
   int sub_max = mode == RRF_STOP_SPECTRAL ? kMaxBlock : p->sub_max;
-  if (sub_max == 0) {
-    sub_max = kMaxBlock;
-    PanelShape sh32;
-    if (p->lookahead != 0 && p->power == 0 && p->panel_mode == kPanelAuto &&
-        std::min(b, kcap) > 32 && (double)m * (double)n * e <= 512.0 * (1 << 20) &&
-        gram_fused_shape(m, 32, p->gram_fused_max, &sh32))
-      sub_max = 32;
-  }
+  if (sub_max == 0) sub_max = kMaxBlock;
   auto sub_width = [&](int64_t kk) -> int64_t {
     if (kk >= kcap) return 0;
     const int64_t be = std::min((kk / b) * b + b, kcap);
@@ -618,15 +601,21 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   // update Y_{i+1} = Q_i^T S_{i+1} as soon as W_i exists (Q_i^T (B Omega) =
   // (Q_i^T B) Omega).  The panel of sub-block i + 1 is then factored by a
   // few workgroups of the update's own launch while the rest update B.
-  // It pays when the panel grid is small: a panel of more than a quarter of
-  // the compute units takes too many slots from the update it runs beside.
+  // It pays when the panel grid is small: a panel of most of the compute
+  // units takes too many slots from the update it runs beside.
   // Power iterations need the whole updated trailing matrix before the
   // sample, so they run without it.
-  // Blocks of at most 32 columns take their panels from the Gram matrix
-  // (la_gram); wider ones column by column.
-  const int alg0 = panel_alg(p, b0);
-  const bool la_gram = alg0 == kPanelGram && pad16(b0) <= 32;
-  bool la = p->lookahead != 0 && power == 0 && kcap > b0 && (alg0 == kPanelGrid || la_gram);
+  // On a large matrix the update is long beside the panel (16384 x 16384 fp64:
+  // 1.25 ms against 0.09 ms) and the slots that the panel and the redundant
+  // panel update take cost more than the panel on its own: 31.5 ms per run
+  // with the look-ahead, 30.8 without; at 4096 x 11008 fp32 (172 MiB) 8.5 with
+  // it, 9.3 without, at 4096 x 4096 fp32 10.4 and 12.4.
+  // A forced column-by-column panel (RRF_PANEL=grid) follows the update in a
+  // launch of its own.
+  const int alg0 = panel_alg(p);
+  const bool la_gram = alg0 == kPanelGram;
+  bool la = p->lookahead != 0 && power == 0 && kcap > b0 && (alg0 == kPanelGrid || la_gram) &&
+            (double)m * (double)n * e <= kLookaheadBytes;
   // The shape of the look-ahead panel of a sub-block (mr rows, width bb).
   auto la_shape = [&](int64_t mr, int64_t bb, PanelShape* sh) -> bool {
     if (la_gram) return gram_fused_shape(mr, (int)bb, p->gram_fused_max, sh);
@@ -787,9 +776,17 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     if (panel_ready) {
       panel_ready = false;
     } else {
-      PanelShape sh;
-      const int route = panel_route(p, mp, (int)bi, &sh);
+      PanelShape sh, shf;
+      int route = panel_route(p, mp, (int)bi, &sh);
       if (route < 0) return RRF_ERR_SHAPE;
+      // Sub-block 0 with look-ahead: its panel beside the first look-ahead
+      // sample, in the shape of a panel inside an update's launch.
+      int occ0 = 0;
+      if (la && la_gram && sub == 0 && b_next > 0 && pad16(b_next) == bp &&
+          la_shape(mp, bi, &shf) && update_gram_supported(0, bp, shf))
+        occ0 = update_gram_occupancy<T>(shf, true);
+      const bool with_sample = occ0 > 0 && (int64_t)occ0 * p->num_cus > shf.G;
+      if (with_sample) sh = shf;
       RRF_LAUNCH(p, RRF_STAGE_PANEL, 0.0, e * mp * bi * ysplits + 8.0 * mp * bi,
                  launch_gather_panel<T>(Yp + yoff, ldb, ldb * 64, ysplits, mp,
                                         (int)bi, bp, sh.rows_pad, p->Ysum,
@@ -801,27 +798,28 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
       pa.Tm = Tm + k * kTLd; pa.ldt = kTLd; pa.tau = tau + k;
       pa.red = p->red; pa.rowj = p->rowj; pa.st = p->st; pa.G = sh.G;
       const double pflops = panel_flops((double)mp, (double)bi);
-      const int occ0 = la && sub == 0 && b_next > 0 && pad16(b_next) == 64 &&
-                               route == kPanelGrid && sample_panel_supported(64, sh)
-                           ? sample_panel_occupancy<T>(sh) : 0;
-      if (occ0 > 0 && (int64_t)occ0 * p->num_cus > sh.G) {
+      if (with_sample) {
         // Look-ahead, sub-block 0: the panel of sub-block 0 and the first
         // look-ahead sample S_1 = A Omega_1 (independent of it) in one
         // launch.  The gather above has already read the partials of Y_0
         // that S_1 replaces.
-        rrf_status rs = sketch_window(k_next, 64, &om_win);
+        rrf_status rs = sketch_window(k_next, bp, &om_win);
         if (rs != RRF_OK) return rs;
         UpdateArgs<T> u1 = u;
         u1.Om = om_win;
-        u1.qp = 64;
+        u1.qp = bp;
         u1.normpart = nullptr;
         const int su1 = upd_splits_fused(m, n, (int64_t)occ0 * p->num_cus - sh.G);
         u1.cols_per_split = round_up(ceil_div(n, su1), 2 * kUpdChunk);
         const int ys1 = (int)ceil_div(n, u1.cols_per_split);
-        pa.epoch_base = next_epoch(p);
+        GramPanelArgs ga{};
+        ga.p = pa;
+        ga.p.epoch_base = next_epoch(p);
+        ga.part = p->gx;
+        ga.sums = p->gx + kGramPartWords;
         const double sfl = 2.0 * m * n * b_next, sby = e * (m * n + m * b_next);
         RRF_LAUNCH(p, RRF_STAGE_SAMPLE, sfl + pflops, sby + 16.0 * mp * bi,
-                   launch_sample_panel<T>(u1, ys1, pa, sh, s));
+                   launch_update_gram<T>(u1, ys1, ga, sh, s));
         spec(RRF_STAGE_SAMPLE, k_next, sfl, sby);
         ysplits = ys1;
         yoff = 0;
@@ -925,12 +923,10 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     ua.W = (T*)p->W; ua.ldw = bp; ua.Om = om_win; ua.ldo = kOmLd; ua.qp = q_s;
     ua.P = Yp; ua.ldp = ldb; ua.split_stride = ldb * 64; ua.s0 = bi;
     ua.normpart = p->normpart;
-    const bool fused = panel_ready && (la_gram ? update_gram_supported(bp, q_s, pan_shape)
-                                               : update_panel_supported(bp, q_s, pan_shape));
+    const bool fused = panel_ready && la_gram && update_gram_supported(bp, q_s, pan_shape);
     int su0 = upd_splits(mp, n, p->num_cus);
     if (fused) {
-      const int occ = la_gram ? update_gram_occupancy<T>(pan_shape)
-                              : update_panel_occupancy<T>(pan_shape);
+      const int occ = update_gram_occupancy<T>(pan_shape, false);
       if (occ > 0)
         su0 = upd_splits_fused(mp, n, (int64_t)occ * p->num_cus - pan_shape.G);
     }
@@ -946,7 +942,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
       set_finalize(p, ua, nparts, at_end ? blk : -1, k_next, kcap, mode, tol, 0);
     if (panel_ready) {
       pan.epoch_base = next_epoch(p);
-      if (fused && la_gram) {
+      if (fused) {
         GramPanelArgs ga{};
         ga.p = pan;
         ga.part = p->gx;
@@ -954,11 +950,6 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
         RRF_LAUNCH(p, RRF_STAGE_UPDATE, upd_flops + pan_flops,
                    2.0 * e * mp * n + pan_bytes,
                    launch_update_gram<T>(ua, su, ga, pan_shape, s));
-        spec(RRF_STAGE_UPDATE, k_next, pan_flops, pan_bytes);
-      } else if (fused) {
-        RRF_LAUNCH(p, RRF_STAGE_UPDATE, upd_flops + pan_flops,
-                   2.0 * e * mp * n + pan_bytes,
-                   launch_update_panel<T>(ua, su, pan, pan_shape, s));
         spec(RRF_STAGE_UPDATE, k_next, pan_flops, pan_bytes);
       } else {
         RRF_LAUNCH(p, RRF_STAGE_UPDATE, upd_flops, 2.0 * e * mp * n,
@@ -1406,11 +1397,10 @@ rrf_status plan_create(rrf_plan_t* plan, int dtype_bits, int64_t m_max, int64_t 
   p->lookahead = 1;
   if (const char* la = std::getenv("RRF_LOOKAHEAD")) p->lookahead = std::atoi(la) != 0;
   // RRF_PANEL selects the panel algorithm: "grid" (column by column, one
-  // grid-wide reduction per column), "gram" (the same reflectors from the
-  // Gram matrix, one grid exchange per sweep of columns), "tsqr" (tall-skinny
-  // QR with Householder reconstruction); the default picks gram or grid by
-  // the block width.  The look-ahead overlaps grid panels and, for blocks of
-  // at most 32 columns, gram panels.
+  // grid-wide reduction per column), "gram" (the default: the same reflectors
+  // from the Gram matrix, one grid exchange per sweep of columns), "tsqr"
+  // (tall-skinny QR with Householder reconstruction).  The look-ahead
+  // factors gram panels inside the update's launch.
   p->panel_mode = kPanelAuto;
   if (const char* pm = std::getenv("RRF_PANEL")) {
     if (std::strcmp(pm, "tsqr") == 0) p->panel_mode = kPanelTsqr;
@@ -1423,15 +1413,11 @@ rrf_status plan_create(rrf_plan_t* plan, int dtype_bits, int64_t m_max, int64_t 
     free_plan(p);
     return RRF_ERR_HIP;
   }
-  // Workgroups the Gram panel may hold inside the update's launch (the
-  // look-ahead of blocks of at most 32 columns): half the compute units, so
-  // that 4096-row panels take 4 rows per thread (its exchange is one per
-  // sweep, so a wider grid costs little; at 4096 x 4096 fp32, b = 32, 128
-  // workgroups measured 17.6 ms per run against 17.8 ms for 64 and 18.3 ms
-  // for 32); RRF_LA_GRAM_WGS overrides.
+  // Workgroups the Gram panel may hold inside the update's launch: half the
+  // compute units (the exchange is one per sweep, so a wider grid costs
+  // little); RRF_LA_GRAM_WGS overrides.
   p->gram_fused_max = std::max(1, p->num_cus / 2);
-  // Sub-blocks of at most RRF_SUBBLOCK (16, 32 or 64) columns; by default
-  // chosen per run from the matrix size (run_impl).
+  // Sub-blocks of at most RRF_SUBBLOCK (16, 32 or 64) columns; 64 by default.
   p->sub_max = 0;
   if (const char* sb = std::getenv("RRF_SUBBLOCK")) {
     const int v = std::atoi(sb);

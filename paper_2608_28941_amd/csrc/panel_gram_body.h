@@ -1,45 +1,69 @@
-// Panel Householder QR with T factor (Alg. 2, geqrt step) computed from the
-// panel's Gram matrix: one grid-wide exchange per sweep of columns instead of
-// one per column.
+// Panel Householder QR with T factor (Alg. 2, geqrt step) from the panel's
+// Gram matrix: one grid-wide exchange per sweep of columns instead of one per
+// column, and the column recurrence of a sweep on 16 x 16 blocks.
 //
 // The reflectors are those of LAPACK dlarfg / geqr2 (same signs, tau, V with
 // unit diagonal); only the inner products they need come from a different
-// place.  Householder steps are orthogonal, so the Gram matrix of the columns
-// over the rows a step touches is invariant under it, and every quantity of
-// the column recurrence (the norm below the diagonal, v_j^T y_k, v_p^T v_j)
-// follows from
+// place.  A sweep starts at column j0 with the current panel X (finished
+// reflector columns before j0) and F = X^T X over the rows >= j0, exchanged
+// across the grid, and runs on F and on the panel's top BP rows alone:
 //
-//   F = X^T X over rows > j,  X = [v_0 .. v_{j-1}  y_j .. y_{b-1}]
+//   * Householder steps are orthogonal, so the Gram matrix of the remaining
+//     columns over the rows >= j0 stays what it was and R (the rows the steps
+//     make final) is its Cholesky factor, with the signs of dlarfg:
+//     R_jj = beta_j = -sign(alpha_j) |R_jj|, alpha_j the current top entry.
+//   * With J the 16 columns of a block, X_JJ their rows of the top block,
+//     X_JJ - R_JJ = V_JJ W_JJ is an LU factorisation (V_JJ unit lower, the
+//     pivots alpha_j - beta_j do not cancel), and below it V = X_J W_JJ^-1.
+//   * The columns K right of J: R_JK = R_JJ^-T F_JK, W_JK = V_JJ^-1 (X_JK -
+//     R_JK), X_K -= V_J W_JK, F_KL -= R_JK^T R_JL.
 //
-// (finished reflector vectors and the not yet factored columns) together
-// with rows 0 .. b-1 of X (the "top" block).  Each step updates F and the top
-// block with O(b^2) work; the bulk rows are updated by the same rank-1
-// recurrence without any inner product.  So after one exchange (F's partial
-// sums over each workgroup's rows, reduced in two phases) every workgroup
-// runs the column recurrence on its own copy of F and the top block, all of
-// them bit for bit alike, and applies it to its rows.
+// So one wavefront factors the 16 x 16 block in registers (Cholesky and LU
+// together, with R^-T, V^-1 and W^-1 built in the same steps; rows of 16
+// lanes hold a block row's 16 columns, four block rows per lane group, so a
+// step needs lane broadcasts only, no LDS and no barrier), and everything
+// else is 16 x 16 tile products on f64 MFMA: the top block and F in LDS, the
+// bulk rows in registers.  Every workgroup runs the sweep on its own copy of
+// F and of the top block, all of them bit for bit alike.
 //
 // Downdating a norm loses relative accuracy when the column has shrunk: the
 // rounding error of F[j][j] after s steps is about s u nu_j, nu_j being the
-// column's norm^2 (rows >= sweep start) when F was last formed.  When
-// F[j][j] < theta nu_j the sweep ends and F is formed again from the current
-// rows (the safeguard LAPACK's dgeqp3 applies to its downdated column norms),
-// so the norm behind each reflector has relative error <= ~64 u / theta and
-// the reflector is orthogonal to that accuracy; a well-conditioned panel
-// needs one exchange.  T (Eq. (4)) comes from the recorded v_p^T v_j and tau
-// by back substitution.
+// column's norm^2 (rows >= sweep start) when F was last formed.  When the
+// norm^2 below the diagonal falls below theta nu_j the sweep ends and F is
+// formed again from the current rows (the safeguard LAPACK's dgeqp3 applies
+// to its downdated column norms), so the norm behind each reflector has
+// relative error <= ~64 u / theta and the reflector is orthogonal to that
+// accuracy; a well-conditioned panel needs one exchange.  The first column of
+// a sweep takes its norm below the diagonal straight from the exchange, so a
+// column that is zero there is seen exactly (tau = 0, H = I; the sweep ends
+// after it).  T (Eq. (4)) comes from the Gram matrix of the finished V (one
+// more exchange, read by one workgroup) and tau.
 //
-// Layout: as the column-by-column panel (thread (k, g) keeps rows
-// w RW + g + (256 / BP) q of column k in registers); F and the top block live
-// in LDS.  Workgroup 0's register copy of rows 0 .. b-1 is not used: those
-// rows are taken from the top block.
+// Layout: 256 threads; a wavefront owns RT tiles of 16 rows, kept in
+// registers as f64 MFMA operands of the transposed frame: lane (g, m) holds
+// row m, columns 16 c + 4 i + g at x[rt][c][i]; the output of a tile product
+// has the same layout, so it is the next product's operand.  Rows 0 .. BP-1
+// (workgroup 0's first tiles) live in the top block; their registers are not
+// used.
+//
+// What bounds it: the exchanges (about 5 us each at 64 workgroups) and the
+// serial 16-column factorisations (5 us each, about 650 cycles a column: one
+// chain of a reciprocal square root, a reciprocal and lane broadcasts).
+// Measured (rrf_panel_qr, the whole call): 16384 x 64 109 us, against 409 us
+// for the column-by-column grid that 64-column panels took before; 4096 x 32
+// 65 us against 85 for the recurrence on all of F with two workgroup barriers
+// per column (1.3 us a column).  In the look-ahead launch at 4096 x 4096 fp32,
+// b = 32: 58 -> 35 us per block.
 //
 // The body runs as a kernel of its own (panel_gram.hip) or on the first
 // workgroups of the look-ahead launch (lookahead.hip); w is the panel
-// workgroup's index, NT the launch's threads per workgroup.
+// workgroup's index.
 
 #pragma once
 
+#include <utility>
+
+#include "lanes.h"
 #include "mfma.h"
 #include "xchg.h"
 
@@ -47,6 +71,14 @@ namespace rrf {
 namespace {
 
 constexpr double kGramTheta = 0.125;
+
+// A lane index the compiler cannot see through: the masks and addresses of
+// one phase of the body are formed there instead of being hoisted out of the
+// sweep loop, where they spill.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
 // Exchanged Gram values: the upper-triangle 16 x 16 tiles of F in the MFMA
 // output layout (tile x, item i, lane l holds F[16 ti + l/16 + 4 i][16 tj +
@@ -56,149 +88,281 @@ struct GramGeom {
   static constexpr int N16 = BP / 16;
   static constexpr int NTL = N16 * (N16 + 1) / 2;
   static constexpr int NSLOT = NTL * 256;
-  static constexpr int NEX = NSLOT + BP * BP;   // then the top block
-  static __device__ __forceinline__ int tile(int ti, int tj) {
+  static constexpr __host__ __device__ __forceinline__ int tile(int ti, int tj) {
     return ti * N16 - ti * (ti - 1) / 2 + (tj - ti);
   }
-  // Slot of F[r][c] (either orientation).
-  static __device__ __forceinline__ int slot(int r, int c) {
-    int a = r, b = c;
-    if ((a >> 4) > (b >> 4) || ((a >> 4) == (b >> 4) && a > b)) {
-      a = c;
-      b = r;
-    }
-    const int ra = a & 15, cb = b & 15;
-    return tile(a >> 4, b >> 4) * 256 + (ra >> 2) * 64 + (ra & 3) * 16 + cb;
-  }
 };
 
-template <int BP, int RPT, int NT>
+constexpr int kTs = 17;   // row stride of a 16 x 16 tile in LDS
+
+template <int BP>
 struct GramLds {
-  static constexpr int GR = NT / BP;
-  double S[BP][BP + 2];         // staged rows for the Gram sums
-  double top[BP][BP + 2];       // rows 0..b-1 of X; above the diagonal of finished
-                                // rows p: v_p^T v_c (c > p), for T
-  double xs[GR][RPT + 2];       // column j at each row group's rows
-  double ujv[2][BP];            // column j of F, by step parity
-  double fdiag[2];              // F[j+1][j+1] before step j, by parity
-  double cw[BP], zv[BP], xt[BP], nu[BP], tau[BP];
-  double colscale[BP];          // 1 / (alpha - beta) of finished columns, else 1
-  double red2[NT];
+  static constexpr int LS = BP + 2;   // staged rows
+  static constexpr int LT = BP + 1;   // top block and W
+  struct Work {
+    double F[GramGeom<BP>::NTL][16 * kTs];   // upper tiles of F; R_JK in place
+    double W[16 * LT];                       // W_JK of the current block
+    double inv[3][16 * kTs];                 // R^-T, V^-1, W^-1
+  };
+  union {
+    double S[64 * LS];            // staged rows for the Gram sums
+    Work k;
+  };
+  double top[BP * LT];            // rows 0..BP-1: V below the diagonal, current
+                                  // columns from the sweep's column on
+  double tau[BP], nu[BP];
+  double red2[256];
+  double fx;                      // norm^2 below the diagonal, sweep's first column
+  int js, stopped;                // of the block just factored
 };
 
-template <int BP, int RPT, int NT>
-__device__ __forceinline__ void panel_gram_body(const GramPanelArgs& ga, const int w) {
+// One 16 x 16 block of a sweep: lane (h, k) holds rows 4 h + i of column k.
+// The four wavefronts run the same Cholesky and LU, and each but the first
+// one of the inverses beside it: R^-T and V^-1 (roles 1 and 2; a row is
+// written to LDS when it is final) and W^-1 (role 3).  V's and W^-1's columns
+// stay unscaled until the block ends (rwl), and entries a later step no
+// longer reads may hold anything, so a step has no per-entry selects.
+struct GramBlock {
+  double f[4], x[4], aux[4];
+  double tau, rwl;  // of the lane's column: tau, and 1 / (alpha - beta)
+  double thr;       // least norm^2 below the diagonal the lane's column may have
+  unsigned todo;    // bit mask of the columns to do
+  int unchecked;    // the column whose norm came straight from the exchange
+  int js;           // columns [o, js) done when the block ends
+};
+
+template <int J>
+__device__ __forceinline__ void gram_block_step(GramBlock& s, double* inv, const int role,
+                                                const int h, const int k) {
+  if (!((s.todo >> J) & 1u)) return;   // uniform
+  constexpr int QJ = J / 4, IJ = J % 4;
+  const double alpha = lane_value<16 * QJ + J>(s.x[IJ]);
+  const double nrm2 = lane_value<16 * QJ + J>(s.f[IJ]);
+  const double xn2 = nrm2 - alpha * alpha;
+  if (J != s.unchecked && !(xn2 >= lane_value<J>(s.thr))) {
+    s.js = J;
+    s.todo = 0;
+    return;
+  }
+  const double fk = row_of<QJ>(s.f[IJ]);    // row J of F and X at the lane's column
+  const double xk = row_of<QJ>(s.x[IJ]);
+  double fr[4], xr[4];                      // column J of F and X at the lane's rows
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    fr[i] = row_lane<J>(s.f[i]);            // (R[J][row] R_JJ, by symmetry)
+    xr[i] = row_lane<J>(s.x[i]);
+  }
+  const double y = fast_rsqrt(nrm2);
+  const double rb = (alpha >= 0.0) ? -y : y;        // 1 / beta
+  const double wjj = fma(-nrm2, rb, alpha);         // alpha - beta
+  const double rw = fast_rcp(wjj);
+  const double fc = fk * (y * y);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s.f[i] = fma(-fr[i], fc, s.f[i]);
+  const double wk = (k > J) ? fma(-fk, rb, xk) : 0.0;   // W_Jk = X_Jk - R_Jk
+  const double wc = rw * wk;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s.x[i] = fma(-xr[i], wc, s.x[i]);
+  s.tau = (k == J) ? -wjj * rb : s.tau;
+  s.rwl = (k == J) ? rw : s.rwl;
+  if (role == 3) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.aux[i] = fma(-row_lane<J>(s.aux[i]), wc, s.aux[i]);
+  } else if (role != 0) {
+    const bool r1 = role == 1;
+    const double a0 = row_of<QJ>(s.aux[IJ]);
+    const double ak = r1 ? a0 * rb : a0;
+    if (h == QJ) inv[J * kTs + k] = ak;
+    const double ac = ak * (r1 ? rb : rw);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.aux[i] = fma(-(r1 ? fr[i] : xr[i]), ac, s.aux[i]);
+  }
+}
+
+template <int... Js>
+__device__ __forceinline__ void gram_block_steps(GramBlock& s, double* inv, const int role,
+                                                 const int h, const int k,
+                                                 std::integer_sequence<int, Js...>) {
+  (gram_block_step<Js>(s, inv, role, h, k), ...);
+}
+
+template <int BP, int RT>
+__device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelArgs& ga,
+                                                const int w) {
   typedef GramGeom<BP> Geo;
-  constexpr int GR = NT / BP;
-  constexpr int RW = GR * RPT;
-  constexpr int QC = BP / GR;        // register slots per staged chunk of BP rows
-  constexpr int BC = BP / 16;        // F block per thread: BR rows x BC columns,
-  constexpr int BR = BP * BP / NT / BC;   // 16 blocks across, NT / 16 down
-  constexpr int QJ = (BP + GR - 1) / GR;
-  constexpr int NW = NT / 64;        // wavefronts
-  constexpr int NTW = (Geo::NTL + NW - 1) / NW;   // Gram tiles per wavefront
-  static_assert(RPT % QC == 0 && RW >= BP, "panel shape");
-  static_assert(BR >= 1 && BR * BC * NT == BP * BP, "F blocks");
-  __shared__ GramLds<BP, RPT, NT> L;
+  typedef GramLds<BP> Lds;
+  constexpr int NB = BP / 16;
+  constexpr int LS = Lds::LS, LT = Lds::LT;
+  constexpr int RW = 64 * RT;
+  // Gram tiles of a wavefront: with one tile the wavefronts split the rows.
+  constexpr bool kSplitRows = Geo::NTL == 1;
+  constexpr int NTW = kSplitRows ? 1 : (Geo::NTL + 3) / 4;
 
   const PanelArgs& a = ga.p;
-  const int t = threadIdx.x;
-  const int k = t % BP, g = t / BP;           // register layout (column k, row group g)
-  const int bi = t / 16, bj = t % 16;         // F / top block (rows BR bi.., cols BC bj..)
-  const int wv = t / 64, l16 = (t % 64) / 16, m16 = t % 16;   // MFMA lane roles
+  const int t0 = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(t0 >> 6);
   const int64_t base = (int64_t)w * RW;
   const int b = a.b, G = a.G;
   const bool forced = waits_forced(a.st);
-
-  double col[RPT];
-  {
-    const double* Yk = a.Y + base + g + (int64_t)k * a.ldy;
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) col[q] = Yk[GR * q];
+  if (forced && G == 1) {   // no wait below: record the forced give-up
+    unsigned spins = 0;
+    keep_waiting(&spins, a.st);
   }
-  if (t < BP) L.colscale[t] = 1.0;
-  double Fr[BR][BC];
-  int tti[NTW], ttj[NTW];
+
+  // This wavefront's rows, and the top block (every workgroup).
+  d4_t x[RT][NB];
+  {
+  const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
 #pragma unroll
-  for (int x = 0; x < NTW; ++x) {
-    int r = wv + NW * x;
-    tti[x] = -1;
-    ttj[x] = -1;
-    for (int i = 0; i < Geo::N16; ++i) {
-      if (r < Geo::N16 - i) {
-        tti[x] = i;
-        ttj[x] = i + r;
-        break;
-      }
-      r -= Geo::N16 - i;
+  for (int rt = 0; rt < RT; ++rt) {
+    const double* Yr = a.Y + base + 16 * (wv * RT + rt) + m16 + (int64_t)g * a.ldy;
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[rt][c][i] = Yr[(int64_t)(16 * c + 4 * i) * a.ldy];
+  }
+  {
+    constexpr int NTOP = BP * BP / 256;
+    double tv[NTOP];
+#pragma unroll
+    for (int q = 0; q < NTOP; ++q) {
+      const int e = t + 256 * q;
+      tv[q] = a.Y[e % BP + (int64_t)(e / BP) * a.ldy];
     }
+#pragma unroll
+    for (int q = 0; q < NTOP; ++q) {
+      const int e = t + 256 * q;
+      L.top[(e % BP) * LT + e / BP] = tv[q];
+    }
+  }
+  if (t < BP) L.tau[t] = 0.0;
   }
 
   unsigned exch = 0;
-  // F (rows > j0) from the current rows: MFMA partial sums over this
-  // workgroup's rows (workgroup 0's rows j0+1 .. b-1 went through the same
-  // updates as the top block), reduced in two phases (workgroup w sums its
-  // slice of slots over all workgroups, then every workgroup reads the slots
-  // of its F entries).  The first call also distributes workgroup 0's rows
-  // 0 .. b-1 as the top block.
-  auto form_gram = [&](const int j0, const bool first) __attribute__((always_inline)) {
+  // Gram matrix of the current rows into L.k.F.  FINAL: of V (unit diagonal,
+  // zeros above), read by workgroup G - 1 only; else over the rows > j0, then
+  // row j0 added (nu, and fx before it is added).
+  auto form_gram = [&](const int j0, auto final_tag) __attribute__((always_inline)) {
+    constexpr bool FINAL = decltype(final_tag)::value;
+    const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
     const unsigned epoch = a.epoch_base + 1u + exch;
     const int par = (int)(exch & 1u);
     ++exch;
     d4_t acc[NTW];
 #pragma unroll
-    for (int x = 0; x < NTW; ++x) acc[x] = d4_t{0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < NTW; ++u) acc[u] = d4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < RPT / QC; ++c) {
+    for (int rt = 0; rt < RT; ++rt) {
       __syncthreads();
+      // Rows below BP come from the top block.
+      const int64_t r = base + 16 * (wv * RT + rt) + m16;
+      double* Sr = L.S + (16 * wv + m16) * LS;
+      if (w == 0 && 16 * (wv * RT + rt) < BP) {   // uniform per wavefront
 #pragma unroll
-      for (int qq = 0; qq < QC; ++qq) {
-        const int q = c * QC + qq;
-        const int64_t r = base + g + GR * q;
-        L.S[g + GR * qq][k] = (r <= j0) ? 0.0 : col[q] * L.colscale[k];
+        for (int c = 0; c < NB; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int k = 16 * c + 4 * i + g;
+            const double v = L.top[r * LT + k];
+            if (FINAL) Sr[k] = (r > k) ? v : (r == k && k < b ? 1.0 : 0.0);
+            else Sr[k] = (r > j0) ? v : 0.0;
+          }
+      } else {
+#pragma unroll
+        for (int c = 0; c < NB; ++c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) Sr[16 * c + 4 * i + g] = x[rt][c][i];
       }
       __syncthreads();
+      if constexpr (kSplitRows) {
 #pragma unroll
-      for (int x = 0; x < NTW; ++x) {
-        if (tti[x] >= 0) {
-#pragma unroll 4
-          for (int s4 = 0; s4 < BP / 4; ++s4) {
-            const double av = L.S[4 * s4 + l16][16 * tti[x] + m16];
-            const double bv = L.S[4 * s4 + l16][16 * ttj[x] + m16];
-            acc[x] = Mfma<double>::op(av, bv, acc[x]);
+        for (int s4 = 0; s4 < 4; ++s4) {
+          const double v = L.S[(16 * wv + 4 * s4 + g) * LS + m16];
+          acc[0] = Mfma<double>::op(v, v, acc[0]);
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < NTW; ++u) {
+          const int tl = wv + 4 * u;
+          if (tl < Geo::NTL) {   // uniform
+            int ti = 0, r0 = tl;
+            while (r0 >= NB - ti) {
+              r0 -= NB - ti;
+              ++ti;
+            }
+            const int tj = ti + r0;
+#pragma unroll 8
+            for (int s4 = 0; s4 < 16; ++s4)
+              acc[u] = Mfma<double>::op(L.S[(4 * s4 + g) * LS + 16 * ti + m16],
+                                        L.S[(4 * s4 + g) * LS + 16 * tj + m16], acc[u]);
           }
         }
       }
     }
+    // One tile: the wavefronts' shares of the rows are added first.
+    if constexpr (kSplitRows) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) L.S[wv * 256 + i * 64 + lane] = acc[0][i];
+      __syncthreads();
+      if (wv == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[0][i] = (L.S[i * 64 + lane] + L.S[256 + i * 64 + lane]) +
+                      (L.S[512 + i * 64 + lane] + L.S[768 + i * 64 + lane]);
+      }
+    }
+    __syncthreads();   // L.S is free: L.k may be written
+    auto put_f = [&](const int slot, double v) __attribute__((always_inline)) {
+      const int tl = slot >> 8, i = (slot >> 6) & 3, ln = slot & 63;
+      const int rr = (ln >> 4) + 4 * i, cc = ln & 15;
+      if (!FINAL) {
+        int ti = 0, r0 = tl;
+        while (r0 >= NB - ti) {
+          r0 -= NB - ti;
+          ++ti;
+        }
+        const int gr = 16 * ti + rr, gc = 16 * (ti + r0) + cc;
+        if (gr == j0 && gc == j0) L.fx = v;
+        v += L.top[j0 * LT + gr] * L.top[j0 * LT + gc];
+        if (gr == gc) L.nu[gr] = v;
+      }
+      L.k.F[tl][rr * kTs + cc] = v;
+    };
+    if (G == 1) {
+#pragma unroll
+      for (int u = 0; u < NTW; ++u) {
+        const int tl = wv + 4 * u;
+        if (tl < Geo::NTL) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) put_f(tl * 256 + i * 64 + lane, acc[u][i]);
+        }
+      }
+      __syncthreads();
+      return;
+    }
     {
       u64* dst = ga.part + ((int64_t)par * G + w) * Geo::NSLOT * 2;
 #pragma unroll
-      for (int x = 0; x < NTW; ++x) {
-        if (tti[x] >= 0) {
-          const int tl = Geo::tile(tti[x], ttj[x]);
+      for (int u = 0; u < NTW; ++u) {
+        const int tl = wv + 4 * u;
+        if (tl < Geo::NTL) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            put_tagged(&dst[(tl * 256 + i * 64 + (t % 64)) * 2], acc[x][i], epoch);
+            put_tagged(&dst[(tl * 256 + i * 64 + lane) * 2], acc[u][i], epoch);
         }
       }
     }
-    if (first && w == 0) {
-#pragma unroll
-      for (int q = 0; q < QJ; ++q) {
-        const int r = g + GR * q;
-        if (r < b)
-          put_tagged(&ga.sums[((int64_t)par * Geo::NEX + Geo::NSLOT + r * BP + k) * 2], col[q], epoch);
-      }
-    }
-    // Phase 2: this workgroup's slice of slots, summed over all workgroups
-    // in a fixed order (nsub threads per slot, then in LDS).
+    u64* sums = ga.sums + (int64_t)par * Geo::NSLOT * 2;
+    // This workgroup's slice of slots, summed over all workgroups in a fixed
+    // order (nsub threads per slot, then in LDS).
     {
       constexpr int NS = Geo::NSLOT;
       const int se = (NS + G - 1) / G;
       const int e0 = w * se;
       const int ne = max(0, min(NS, e0 + se) - e0);
-      const int nsub = max(1, min(16, NT / max(ne, 1)));
-      const int per = NT / nsub;
+      const int nsub = max(1, min(16, 256 / max(ne, 1)));
+      const int per = 256 / nsub;
       for (int p0 = 0; p0 < ne; p0 += per) {
         const int el = p0 + t % per, sub = t / per;
         double s = 0.0;
@@ -230,260 +394,299 @@ __device__ __forceinline__ void panel_gram_body(const GramPanelArgs& ga, const i
         if (t < per && p0 + t < ne) {
           double tot = 0.0;
           for (int sb = 0; sb < nsub; ++sb) tot += L.red2[sb * per + t];
-          put_tagged(&ga.sums[((int64_t)par * Geo::NEX + e0 + p0 + t) * 2], tot, epoch);
+          put_tagged(&sums[(int64_t)(e0 + p0 + t) * 2], tot, epoch);
         }
         __syncthreads();
       }
     }
-    // Phase 3: every thread reads the sums of its F entries (and, the first
-    // time, its entries of the top block).
+    if (FINAL && w != G - 1) return;
+    // The sums (every workgroup that goes on reads all of them).
     {
-      constexpr int NQ = BR * BC;
+      u64 hi[Geo::NTL], lo[Geo::NTL];
       unsigned spins = 0;
-      auto fetch = [&](const bool topblk) __attribute__((always_inline)) {
-        u64 hi[NQ], lo[NQ];
-        bool ok;
-        do {
+      bool ok;
+      do {
 #pragma unroll
-          for (int i = 0; i < BR; ++i)
+        for (int q = 0; q < Geo::NTL; ++q) {
+          const u64* p = sums + (int64_t)(t + 256 * q) * 2;
+          hi[q] = get_word(p);
+          lo[q] = get_word(p + 1);
+        }
+        ok = true;
 #pragma unroll
-            for (int jj = 0; jj < BC; ++jj) {
-              const int r = BR * bi + i, c = BC * bj + jj;
-              const int idx = (topblk && r < b) ? Geo::NSLOT + r * BP + c : Geo::slot(r, c);
-              const u64* q = ga.sums + ((int64_t)par * Geo::NEX + idx) * 2;
-              hi[i * BC + jj] = get_word(q);
-              lo[i * BC + jj] = get_word(q + 1);
-            }
-          ok = true;
+        for (int q = 0; q < Geo::NTL; ++q) ok = ok && tagged(hi[q], epoch) && tagged(lo[q], epoch);
+      } while ((!ok || forced) && keep_waiting(&spins, a.st));
 #pragma unroll
-          for (int i = 0; i < NQ; ++i) ok = ok && tagged(hi[i], epoch) && tagged(lo[i], epoch);
-        } while ((!ok || forced) && keep_waiting(&spins, a.st));
-#pragma unroll
-        for (int i = 0; i < BR; ++i)
-#pragma unroll
-          for (int jj = 0; jj < BC; ++jj) {
-            const double v = untag(hi[i * BC + jj], lo[i * BC + jj]);
-            if (!topblk) Fr[i][jj] = v;
-            else L.top[BR * bi + i][BC * bj + jj] = (BR * bi + i < b) ? v : 0.0;
-          }
-      };
-      fetch(false);
-      if (first) fetch(true);
+      for (int q = 0; q < Geo::NTL; ++q) put_f(t + 256 * q, untag(hi[q], lo[q]));
     }
-  };
-
-  // Exports for step jn (parity pn) by the owners of the entries: column jn
-  // of F, and F[jn+1][jn+1] (the next pivot's norm before step jn).
-  auto export_step = [&](const int jn, const int pn) __attribute__((always_inline)) {
-    const int jb = jn / BC, jo = jn % BC;
-    const int j1r = (jn + 1) / BR, j1i = (jn + 1) % BR;
-    const int j1c = (jn + 1) / BC, j1o = (jn + 1) % BC;
-    // jo, j1i, j1o are the same in every thread: the branches below are
-    // uniform, and every register index is a constant (no dynamically
-    // indexed array).
-    if (bj == jb) {
-#pragma unroll
-      for (int jj = 0; jj < BC; ++jj)
-        if (jj == jo)
-#pragma unroll
-          for (int i = 0; i < BR; ++i) L.ujv[pn][BR * bi + i] = Fr[i][jj];
-    }
-    if (bi == j1r && bj == j1c) {
-#pragma unroll
-      for (int i = 0; i < BR; ++i)
-#pragma unroll
-        for (int jj = 0; jj < BC; ++jj)
-          if (i == j1i && jj == j1o) L.fdiag[pn] = Fr[i][jj];
-    }
-  };
-  // dlarfg scalars of a step from alpha = top[j][j] and ||x||^2 = F[j][j]
-  // (every thread computes them from the same values); flag: the downdated
-  // norm has cancelled and F must be formed again first.
-  auto scalars = [&](const double alpha, const double xn2, const double nuj, const bool fresh,
-                     double& flag, double& tau_j, double& scale) __attribute__((always_inline)) {
-    flag = 0.0;
-    tau_j = 0.0;
-    scale = 0.0;
-    if (!fresh && nuj > 0.0 && !(xn2 >= kGramTheta * nuj)) {
-      flag = 1.0;
-    } else if (xn2 > 0.0) {
-      const double nrm = sqrt(alpha * alpha + xn2);
-      const double beta = (alpha >= 0.0) ? -nrm : nrm;
-      tau_j = (beta - alpha) / beta;
-      scale = 1.0 / (alpha - beta);
-    }
-  };
-  // After a Gram formation at j0: exports, then the reference norms
-  // nu_c = F[c][c] + top[j0][c]^2 (the column's norm^2 over rows >= j0).
-  double s_flag = 0.0, s_tau = 0.0, s_scale = 0.0;   // scalars of the next step
-  auto after_form = [&](const int j0) __attribute__((always_inline)) {
-    export_step(j0, j0 & 1);
-    __syncthreads();
-    scalars(L.top[j0][j0], L.ujv[j0 & 1][j0], 0.0, true, s_flag, s_tau, s_scale);
-#pragma unroll
-    for (int i = 0; i < BR; ++i)
-#pragma unroll
-      for (int jj = 0; jj < BC; ++jj) {
-        const int r = BR * bi + i, c = BC * bj + jj;
-        if (r == c) L.nu[c] = Fr[i][jj] + L.top[j0][c] * L.top[j0][c];
-      }
     __syncthreads();
   };
 
-  form_gram(0, true);
-  after_form(0);
-  int j = 0;
-  // Column steps in an inner loop of their own; a cancelled pivot norm leaves
-  // it to form F again (the formation code stays out of the step loop).
-  for (;;) {
-  while (j < b && s_flag == 0.0) {
-    const int p = j & 1;
-    const double tau_j = s_tau, scale = s_scale;
-    // The next pivot before this step: F[j+1][j+1] and top[j+1][j+1] (row
-    // j + 1 is not written before the barrier below).
-    const double fd1 = L.fdiag[p];
-    const double td1 = (j + 1 < b) ? L.top[j + 1][j + 1] : 0.0;
-    // Per column: c_k = tau w_k scale with w_k = v_j^T y_k (k > j), v_p^T v_j
-    // (p < j) for T, column j at the top rows below the diagonal, and row
-    // j + 1 after this step (removed from F).
-    if (t < BP) {
-      const int kk = t;
-      // Every read first: the only top entry written here, (kk, j) for
-      // kk < j, is none of the entries read (rows j and j + 1, and (kk, j)
-      // for kk > j), so no read waits for a write.
-      const int j1 = (j + 1 < BP) ? j + 1 : j;
-      const double tjk = L.top[j][kk], ujk = L.ujv[p][kk], tkj = L.top[kk][j];
-      const double xj1 = L.top[j1][j], yk = L.top[j1][kk];
-      const double wv2 = tjk + scale * ujk;
-      const double cwk = (kk > j && kk < b) ? tau_j * wv2 * scale : 0.0;
-      L.cw[kk] = cwk;
-      if (kk < j) L.top[kk][j] = wv2;   // v_kk^T v_j, for T
-      L.xt[kk] = (kk > j && kk < b) ? tkj : 0.0;
-      double zk = 0.0;
-      if (j + 1 < b && kk < b)
-        zk = (kk > j) ? yk - cwk * xj1 : ((kk == j) ? scale * xj1 : yk);
-      L.zv[kk] = zk;
-      if (kk == j) {
-        L.tau[j] = tau_j;
-        L.colscale[j] = scale;
-      }
+  // Tile product D[g + 4 i][m16] of LDS tiles (row strides la, lb), added to
+  // c; AT: the transpose of A.
+  auto mm = [&](const double* A, const int la, const bool at, const double* B, const int lb,
+                const int g, const int m16, d4_t c) __attribute__((always_inline)) -> d4_t {
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) {
+      const int kk = 4 * s4 + g;
+      const double av = at ? A[kk * la + m16] : A[m16 * la + kk];
+      c = Mfma<double>::op(av, B[kk * lb + m16], c);
     }
-    if (k == j) {
+    return c;
+  };
+
+  // The bulk rows under the column operations of block J (a compile-time
+  // constant: x stays in registers): X_J <- X_J a4, X_K <- X_K - V_J W_JK.
+  auto bulk = [&](auto jtag) __attribute__((always_inline)) {
+    constexpr int J = decltype(jtag)::value;
+    const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
+    (void)t;
+    double av[4];
 #pragma unroll
-      for (int q = 0; q < RPT; ++q) L.xs[g][q] = col[q];
+    for (int s4 = 0; s4 < 4; ++s4) av[s4] = L.k.inv[2][(4 * s4 + g) * kTs + m16];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      d4_t d = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) d = Mfma<double>::op(av[s4], x[rt][J][s4], d);
+      x[rt][J] = d;
     }
-    __syncthreads();
-    // Scalars of step j + 1: its pivot after this step, by the formulas of
-    // the F and top updates below (every thread, from the same values).
-    if (j + 1 < b) {
-      const double fjj0 = L.ujv[p][j];
-      const double c1 = L.cw[j + 1], u1 = L.ujv[p][j + 1], z1 = L.zv[j + 1];
-      double f = fd1 - c1 * u1;
-      f = f - c1 * u1;
-      f = f + (c1 * c1) * fjj0;
-      const double xn2n = f - z1 * z1;
-      const double alphan = td1 - c1 * L.xt[j + 1];
-      scalars(alphan, xn2n, L.nu[j + 1], false, s_flag, s_tau, s_scale);
+#pragma unroll
+    for (int K = J + 1; K < NB; ++K) {
+      double wvv[4];
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) wvv[s4] = -L.k.W[(4 * s4 + g) * LT + 16 * K + m16];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4)
+          x[rt][K] = Mfma<double>::op(wvv[s4], x[rt][J][s4], x[rt][K]);
     }
-    // Apply the step: registers (this workgroup's rows), F and top blocks.
-    {
-      // Columns k > j lose c_k x_j (c_k = 0 elsewhere).  Column j keeps its
-      // unscaled values: v_j = colscale_j x_j is formed where it is read
-      // (Gram sums, output).
-      const double ck = L.cw[k];
+  };
+
+  const int nbb = (b + 15) / 16;   // blocks with a column of the panel
+  int j0 = 0;
+  while (j0 < b) {                 // sweeps (uniform)
+    form_gram(j0, std::false_type{});
+    bool first = true;
+    int J = j0 / 16;
+    for (; J < nbb; ++J) {
+      const int o = max(j0 - 16 * J, 0);
+      double* topJ = L.top + 16 * J * LT;
+      {
+        const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
+        GramBlock s;
+        const double* Fj = L.k.F[Geo::tile(J, J)];
 #pragma unroll
-      for (int q = 0; q < RPT; ++q) col[q] = col[q] - ck * L.xs[g][q];
-    }
-    {
-      const double fjj = L.ujv[p][j];
-      double cwc[BC], ujc[BC], zc[BC];
+        for (int i = 0; i < 4; ++i) {
+          const int r = 4 * g + i;
+          s.f[i] = Fj[r * kTs + m16];
+          s.x[i] = topJ[r * LT + 16 * J + m16];
+          s.aux[i] = (r == m16) ? 1.0 : 0.0;
+        }
+        // (At least the least positive number: a norm of zero ends the sweep.)
+        s.thr = fmax(kGramTheta * L.nu[16 * J + m16], 4.9406564584124654e-324);
+        s.tau = 0.0;
+        s.rwl = 1.0;
+        const int nb = min(16, b - 16 * J);
+        s.js = nb;
+        s.unchecked = first ? o : -1;
+        s.todo = ((1u << nb) - 1u) & ~((1u << o) - 1u);
+        if (first && !(L.fx > 0.0)) {
+          // Nothing below the diagonal in the sweep's first column: H = I,
+          // V's column zero, tau = 0, and the sweep ends after it.
+          s.js = o + 1;
+          s.todo = 0;
+          if (m16 == o) s.rwl = 0.0;
+        }
+        const bool whole = s.js == nb;
+        __syncthreads();   // every wavefront has read the block
+        gram_block_steps(s, L.k.inv[max(wv - 1, 0)], wv, g, m16,
+                         std::make_integer_sequence<int, 16>{});
 #pragma unroll
-      for (int jj = 0; jj < BC; ++jj) {
-        const int c = BC * bj + jj;
-        cwc[jj] = L.cw[c];
-        ujc[jj] = L.ujv[p][c];
-        zc[jj] = L.zv[c];
-      }
-      const bool top_rows = (BR * bi + BR - 1 > j) && (BR * bi < b);
-#pragma unroll
-      for (int i = 0; i < BR; ++i) {
-        const int r = BR * bi + i;
-        const double cwr = L.cw[r], ujr = L.ujv[p][r], zr = L.zv[r];
-        const double sr = (r == j) ? scale : 1.0;
-#pragma unroll
-        for (int jj = 0; jj < BC; ++jj) {
-          const int c = BC * bj + jj;
-          const double sc = (c == j) ? scale : 1.0;
-          double f = Fr[i][jj] - cwc[jj] * ujr;
-          f = f - cwr * ujc[jj];
-          f = f + (cwr * cwc[jj]) * fjj;
-          Fr[i][jj] = (sr * sc) * f - zr * zc[jj];
+        for (int i = 0; i < 4; ++i) {
+          const int r = 4 * g + i;
+          // Rows above the diagonal of a finished column are not read again.
+          if (wv == 0) topJ[r * LT + 16 * J + m16] = s.x[i] * s.rwl;
+          if (wv == 3) L.k.inv[2][r * kTs + m16] = s.aux[i] * s.rwl;
+        }
+        if (t >= o && t < s.js) L.tau[16 * J + t] = s.tau;
+        if (t == 0) {
+          L.js = s.js;
+          L.stopped = (whole && s.todo != 0) ? 0 : 1;
         }
       }
-      if (top_rows) {
+      __syncthreads();
+      const int js = L.js;
+      const bool stopped = L.stopped != 0;
+      first = false;
+      // R_JK over F_JK (rows [o, js), the others zero) and V in the top rows
+      // below the block.
+      {
+        const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
+        (void)t;
+        const int nk = NB - 1 - J;
+        for (int u = wv; u < 2 * nk; u += 4) {
+          if (u < nk) {
+            double* Fk = L.k.F[Geo::tile(J, J + 1 + u)];
+            const d4_t d = mm(L.k.inv[0], kTs, false, Fk, kTs, g, m16, d4_t{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
-        for (int i = 0; i < BR; ++i) {
-          const int r = BR * bi + i;
-          if (r > j && r < b) {
-            // The row's entries are read together, then written (each entry
-            // belongs to one thread).
-            const double xr = L.xt[r];
-            double tv[BC];
-#pragma unroll
-            for (int jj = 0; jj < BC; ++jj) tv[jj] = L.top[r][BC * bj + jj];
-#pragma unroll
-            for (int jj = 0; jj < BC; ++jj) {
-              const int c = BC * bj + jj;
-              L.top[r][c] = (c == j) ? scale * xr : tv[jj] - cwc[jj] * xr;
+            for (int i = 0; i < 4; ++i) {
+              const int r = g + 4 * i;
+              Fk[r * kTs + m16] = (r >= o && r < js) ? d[i] : 0.0;
             }
+          } else {
+            double* X = L.top + 16 * (J + 1 + u - nk) * LT + 16 * J;
+            const d4_t d = mm(X, LT, false, L.k.inv[2], kTs, g, m16, d4_t{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+            for (int i = 0; i < 4; ++i) X[(g + 4 * i) * LT + m16] = d[i];
+          }
+        }
+        if (nk > 0) __syncthreads();
+        // W_JK = V_JJ^-1 (X_JK - R_JK), rows [o, js).
+        for (int u = wv; u < nk; u += 4) {
+          const int K = J + 1 + u;
+          const double* Fk = L.k.F[Geo::tile(J, K)];
+          d4_t d = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int s4 = 0; s4 < 4; ++s4) {
+            const int kk = 4 * s4 + g;
+            d = Mfma<double>::op(L.k.inv[1][m16 * kTs + kk],
+                                 topJ[kk * LT + 16 * K + m16] - Fk[kk * kTs + m16], d);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int r = g + 4 * i;
+            L.k.W[r * LT + 16 * K + m16] = (r >= o && r < js) ? d[i] : 0.0;
+          }
+        }
+        if (nk > 0) __syncthreads();
+        // X_IK -= V_IJ W_JK in the top rows below the block (and in the
+        // block's own rows >= js when the sweep ends here); F_KL -= R_JK^T
+        // R_JL when it goes on.
+        const int nt = nk * nk;
+        const int extra = stopped ? nk : nk * (nk + 1) / 2;
+        for (int u = wv; u < nt + extra; u += 4) {
+          if (u < nt) {
+            const int I = J + 1 + u / nk, K = J + 1 + u % nk;
+            double* X = L.top + 16 * I * LT;
+            const d4_t d = mm(X + 16 * J, LT, false, L.k.W + 16 * K, LT,
+                              g, m16, d4_t{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+            for (int i = 0; i < 4; ++i) X[(g + 4 * i) * LT + 16 * K + m16] -= d[i];
+          } else if (stopped) {
+            const int K = J + 1 + u - nt;
+            d4_t d = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s4 = 0; s4 < 4; ++s4) {
+              const int kk = 4 * s4 + g;
+              const double v = topJ[m16 * LT + 16 * J + kk];
+              d = Mfma<double>::op((kk >= o && kk < js) ? v : 0.0, L.k.W[kk * LT + 16 * K + m16], d);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int r = g + 4 * i;
+              if (r >= js) topJ[r * LT + 16 * K + m16] -= d[i];
+            }
+          } else {
+            int v = u - nt, ti = 0;
+            while (v >= nk - ti) {
+              v -= nk - ti;
+              ++ti;
+            }
+            const int K = J + 1 + ti, M = K + v;
+            double* Fk = L.k.F[Geo::tile(K, M)];
+            const d4_t d = mm(L.k.F[Geo::tile(J, K)], kTs, true, L.k.F[Geo::tile(J, M)], kTs,
+                              g, m16, d4_t{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Fk[(g + 4 * i) * kTs + m16] -= d[i];
           }
         }
       }
+      if (J == 0) bulk(std::integral_constant<int, 0>{});
+      if constexpr (NB > 1)
+        if (J == 1) bulk(std::integral_constant<int, 1>{});
+      if constexpr (NB > 2) {
+        if (J == 2) bulk(std::integral_constant<int, 2>{});
+        if (J == 3) bulk(std::integral_constant<int, 3>{});
+      }
+      __syncthreads();
+      if (stopped) {
+        j0 = 16 * J + js;
+        break;
+      }
     }
-    if (j + 1 < b) export_step(j + 1, p ^ 1);
-    __syncthreads();
-    ++j;
-  }
-  if (j >= b) break;
-  form_gram(j, false);
-  after_form(j);
+    if (J == nbb) j0 = b;
   }
 
-  // The top block holds rows 0 .. b-1 of V below the diagonal and v_p^T v_c
-  // above it.
+  const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
   // V with explicit unit diagonal and zeros above / beyond b.
 #pragma unroll
-  for (int q = 0; q < RPT; ++q) {
-    const int64_t r = base + g + GR * q;
+  for (int rt = 0; rt < RT; ++rt) {
+    const int64_t r = base + 16 * (wv * RT + rt) + m16;
     if (r < a.m) {
-      double v = 0.0;
-      if (k < b) {
-        if (r < b) v = (r > k) ? L.top[r][k] : (r == k ? 1.0 : 0.0);
-        else v = col[q] * L.colscale[k];
-      }
-      a.V[r + k * a.ldv] = v;
+      const bool top = w == 0 && 16 * (wv * RT + rt) < BP;
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = 16 * c + 4 * i + g;
+          double v = x[rt][c][i];
+          if (top) v = (r > k) ? L.top[r * LT + k] : (r == k && k < b ? 1.0 : 0.0);
+          a.V[r + (int64_t)k * a.ldv] = v;
+        }
     }
   }
-  // T (Eq. (4)) from v_p^T v_c and tau: T[c][c] = tau_c, T[i][c] =
-  // -tau_i sum_{i < p <= c} (v_i^T v_p) T[p][c] (tau_i = 0 gives a zero row).
-  if (w == G - 1 && t < BP) {
-    const int c = t;
-    double tc[BP];
+
+  // T (Eq. (4)) from S = V^T V and tau: T[c][c] = tau_c, T[i][c] = -tau_i
+  // sum_{i < p <= c} S[i][p] T[p][c] (tau_i = 0 gives a zero row); within the
+  // diagonal blocks by back substitution, one column per thread, then
+  // T_JK = -T_JJ sum_{J < M <= K} S_JM T_MK by block diagonals.
+  form_gram(0, std::true_type{});
+  if (w != G - 1) return;
+  double* Tl = L.top;
+  if (t < BP) {
+    const int J = t / 16, cc = t % 16;
+    const double* Sj = L.k.F[Geo::tile(J, J)];
+    double tc[16];
 #pragma unroll
-    for (int i = BP - 1; i >= 0; --i) {
+    for (int i = 15; i >= 0; --i) {
       double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-      for (int pp = i + 1; pp < BP; pp += 2) {
-        s0 += ((pp <= c) ? L.top[i][pp] : 0.0) * tc[pp];
-        if (pp + 1 < BP) s1 += ((pp + 1 <= c) ? L.top[i][pp + 1] : 0.0) * tc[pp + 1];
+      for (int p = i + 1; p < 16; p += 2) {
+        s0 += Sj[i * kTs + p] * tc[p];
+        if (p + 1 < 16) s1 += Sj[i * kTs + p + 1] * tc[p + 1];
       }
-      const double ti2 = L.tau[i];
-      tc[i] = (c < b && i < c) ? -ti2 * (s0 + s1) : ((c < b && i == c) ? ti2 : 0.0);
+      const double ti = L.tau[16 * J + i];
+      tc[i] = (i < cc) ? -ti * (s0 + s1) : (i == cc ? ti : 0.0);
     }
 #pragma unroll
-    for (int i = 0; i < BP; ++i) a.Tm[i + (int64_t)c * a.ldt] = tc[i];
-    if (c < b) a.tau[c] = L.tau[c];
+    for (int i = 0; i < 16; ++i) Tl[(16 * J + i) * LT + t] = tc[i];
   }
+  __syncthreads();
+#pragma unroll 1
+  for (int d = 1; d < NB; ++d) {
+    for (int J = wv; J < NB - d; J += 4) {
+      const int K = J + d;
+      d4_t s = d4_t{0.0, 0.0, 0.0, 0.0};
+      for (int M = J + 1; M <= K; ++M)
+        s = mm(L.k.F[Geo::tile(J, M)], kTs, false, Tl + 16 * M * LT + 16 * K, LT, g, m16, s);
+      d4_t o = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4)
+        o = Mfma<double>::op(-Tl[(16 * J + m16) * LT + 16 * J + 4 * s4 + g], s[s4], o);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Tl[(16 * J + g + 4 * i) * LT + 16 * K + m16] = o[i];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < BP * BP / 256; ++q) {
+    const int e = t + 256 * q;
+    const int i = e % BP, c = e / BP;
+    a.Tm[i + (int64_t)c * a.ldt] = (i / 16 <= c / 16) ? Tl[i * LT + c] : 0.0;
+  }
+  if (t < b) a.tau[t] = L.tau[t];
 }
 
 }  // namespace

@@ -212,14 +212,19 @@ bool tsqr_shape(int64_t m, int b, TsqrShape* out);
 hipError_t launch_panel_tsqr(const PanelArgs& a, const TsqrShape& sh, double* scratch,
                              hipStream_t s);
 
-// Panel from the Gram matrix (one grid exchange per sweep of columns); the
-// scratch holds 2 x G x NS tagged partial sums (part) and 2 x (NS + bp^2)
-// tagged sums (sums), NS = 256 x the upper-triangle 16 x 16 tiles of a
-// bp x bp matrix (2560 for bp = 64), zeroed once.
+// Panel from the Gram matrix (one grid exchange per sweep of columns, and
+// one for T); the scratch holds 2 x G x NS tagged partial sums (part) and
+// 2 x NS tagged sums (sums), NS = 256 x the upper-triangle 16 x 16 tiles of a
+// bp x bp matrix (2560 for bp = 64), zeroed once.  A shape's rpt is the row
+// tiles (of 16 rows) per wavefront.
 constexpr int kMaxGramWGs = 256;
 constexpr int64_t kGramSlots = 10 * 256;
 constexpr int64_t kGramPartWords = 2LL * kMaxGramWGs * kGramSlots * 2;
-constexpr int64_t kGramSumWords = 2LL * (kGramSlots + 64 * 64) * 2;
+constexpr int64_t kGramSumWords = 2LL * kGramSlots * 2;
+// Columns x row tiles of a Gram panel inside the update's launch: its
+// registers (twice that) beside the rest of the body must leave two
+// workgroups per compute unit.
+constexpr int kGramFusedRegs = 256;
 struct GramPanelArgs {
   PanelArgs p;                 // Y, ldy, m, b, V, Tm, tau, st, G, epoch_base
   unsigned long long* part;
@@ -276,34 +281,16 @@ struct ThinApplyArgs {
 };
 hipError_t launch_thin_apply(ThinApplyArgs a, int num_cus, hipStream_t s);
 
-// Look-ahead: the update (store, sample width qp) and the panel of the next
-// block in one launch; supported when bp == qp == the panel's padded width.
-bool update_panel_supported(int bp, int qp, const PanelShape& sh);
-template <typename T>
-hipError_t launch_update_panel(const UpdateArgs<T>& ua, int nsplit,
-                               const PanelArgs& pa, const PanelShape& sh,
-                               hipStream_t s);
-// Workgroups of that launch resident per compute unit (0 if unknown).
-template <typename T>
-int update_panel_occupancy(const PanelShape& sh);
-// Block 0: the first look-ahead sample (ua.bp = 0, no store, qp = 64) and the
-// panel of block 0 in one launch; supported for 64-column panels.
-bool sample_panel_supported(int qp, const PanelShape& sh);
-template <typename T>
-hipError_t launch_sample_panel(const UpdateArgs<T>& ua, int nsplit,
-                               const PanelArgs& pa, const PanelShape& sh,
-                               hipStream_t s);
-template <typename T>
-int sample_panel_occupancy(const PanelShape& sh);
-// Look-ahead for blocks of at most 32 columns: the update and the next
-// block's Gram panel (256 threads per workgroup) in one launch; supported
-// when bp == qp == the panel's padded width (16 or 32).
+// Look-ahead: the update and the next block's Gram panel in one launch,
+// supported when bp == qp == the panel's padded width; or (ua.bp = 0, no
+// store) the first look-ahead sample and the panel of block 0.
 bool update_gram_supported(int bp, int qp, const PanelShape& sh);
 template <typename T>
 hipError_t launch_update_gram(const UpdateArgs<T>& ua, int nsplit, const GramPanelArgs& ga,
                               const PanelShape& sh, hipStream_t s);
+// Workgroups of that launch resident per compute unit (0 if unknown).
 template <typename T>
-int update_gram_occupancy(const PanelShape& sh);
+int update_gram_occupancy(const PanelShape& sh, bool sample_only);
 // Shape of a Gram panel inside that launch: the fewest rows per thread whose
 // grid has at most max_wgs workgroups.
 bool gram_fused_shape(int64_t m, int b, int max_wgs, PanelShape* out);

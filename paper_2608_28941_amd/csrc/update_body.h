@@ -68,9 +68,22 @@ template <> struct Buf<float> {
 // 256 threads; wavefront w owns RT adjacent 16-row tiles, so every staged W
 // and Omega value read from LDS feeds RT MFMAs.
 // ---------------------------------------------------------------------------
+
+// Staged W and Omega chunks, double buffered: chunk c is read from buffer
+// c % 2 while chunk c + 1 is written to the other one, so one barrier per
+// chunk separates both the reads from the next overwrite and the writes from
+// the next reads.
+template <typename T, int BP, int QP>
+struct UpdLds {
+  T wl[2][kUpdChunk * (BP > 0 ? BP + 1 : 1)];
+  T ol[2][kUpdChunk * (QP > 0 ? QP + 1 : 1)];
+  double nred[2][4];
+};
+
 template <typename T, int BP, int QP, bool STORE>
-__device__ __forceinline__ void update_body(const UpdateArgs<T>& a, const unsigned rb,
-                                            const unsigned split, const unsigned nrb) {
+__device__ __forceinline__ void update_body(UpdLds<T, BP, QP>& L, const UpdateArgs<T>& a,
+                                            const unsigned rb, const unsigned split,
+                                            const unsigned nrb) {
   typedef typename Mfma<T>::acc_t acc_t;
   constexpr int RT = kUpdRowTiles;
   constexpr int NP4 = BP / 4;        // K-steps of the rank-b update
@@ -80,13 +93,9 @@ __device__ __forceinline__ void update_body(const UpdateArgs<T>& a, const unsign
   constexpr int NCT = kUpdChunk / 16;
   constexpr int E = (int)sizeof(T);
   static_assert(kUpdRows == 64 * RT, "workgroup height");
-  // Staged W and Omega chunks, double buffered: chunk c is read from buffer
-  // c % 2 while chunk c + 1 is written to the other one, so one barrier per
-  // chunk separates both the reads from the next overwrite and the writes
-  // from the next reads.
-  __shared__ T wl[2][kUpdChunk * (BP > 0 ? LDW : 1)];
-  __shared__ T ol[2][kUpdChunk * (QP > 0 ? LDO : 1)];
-  __shared__ double nred[2][4];
+  auto& wl = L.wl;
+  auto& ol = L.ol;
+  auto& nred = L.nred;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m16 = lane & 15, g = lane >> 4;

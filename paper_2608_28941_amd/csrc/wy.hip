@@ -353,7 +353,8 @@ __global__ __launch_bounds__(256) void formw128_kernel(FormWArgs<double> a) {
 
 template <typename T, int BP, int QP, bool STORE>
 __global__ __launch_bounds__(256, 2) void update_kernel(UpdateArgs<T> a) {
-  update_body<T, BP, QP, STORE>(a, blockIdx.x, blockIdx.y, gridDim.x);
+  __shared__ UpdLds<T, BP, QP> L;
+  update_body<T, BP, QP, STORE>(L, a, blockIdx.x, blockIdx.y, gridDim.x);
 }
 
 template <typename T, int BP, int QP>
