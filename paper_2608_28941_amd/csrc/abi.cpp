@@ -98,7 +98,7 @@ Sizes compute_sizes(rrf_dtype dt, int64_t m_max, int64_t n_max, int64_t b_max,
   // Spectral-norm estimate: the gathered next sample, the Gram partials;
   // power iterations: their scaled identity.
   z.Yest = (size_t)z.ldysum * 64 * 8;
-  z.spec = (size_t)kMaxSpecWGs * 4096 * 8;
+  z.spec = (size_t)(kMaxSpecWGs + 2) * 4096 * 8;
   z.Tpow = (size_t)64 * 64 * 8;
   // Explicit-Q pass: merged T of block groups (kGroupMax rows per column)
   // and the group list (blocks of at least one column each).
@@ -1756,7 +1756,8 @@ rrf_status rrf_subspace_map(rrf_plan_t plan, const void* Qnew, int64_t ldqn,
   // Grid limits of the tiled kernels (64 x 64 output tiles).
   if (ceil_div(n, 64) > 65535 || ceil_div(r_old, 64) > 65535) return RRF_ERR_SHAPE;
   const int nsplit = map_splits(r_new, r_old, m, plan->num_cus);
-  const size_t need = (size_t)(nsplit + 1) * (size_t)r_new * (size_t)r_old * e;
+  const size_t celems = (size_t)map_c_elems(r_new, r_old);
+  const size_t need = (size_t)(nsplit + 1) * celems * e;
   if (need > plan->map_c_bytes) {
     if (plan->map_c) {
       (void)hipFree(plan->map_c);
@@ -1774,12 +1775,12 @@ rrf_status rrf_subspace_map(rrf_plan_t plan, const void* Qnew, int64_t ldqn,
     double* Cp = (double*)plan->map_c;
     he = launch_subspace_map<double>((const double*)Qnew, ldqn, r_new, (const double*)Qold,
                                      ldqo, r_old, (const double*)M, ldm, m, n, (double*)out,
-                                     ldo, Cp, Cp + (size_t)nsplit * r_new * r_old, nsplit, s);
+                                     ldo, Cp, Cp + (size_t)nsplit * celems, nsplit, s);
   } else {
     float* Cp = (float*)plan->map_c;
     he = launch_subspace_map<float>((const float*)Qnew, ldqn, r_new, (const float*)Qold, ldqo,
                                     r_old, (const float*)M, ldm, m, n, (float*)out, ldo, Cp,
-                                    Cp + (size_t)nsplit * r_new * r_old, nsplit, s);
+                                    Cp + (size_t)nsplit * celems, nsplit, s);
   }
   return he == hipSuccess ? RRF_OK : hip_fail(he);
 }

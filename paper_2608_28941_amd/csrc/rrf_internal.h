@@ -305,7 +305,7 @@ hipError_t launch_gather_panel(const T* P, int64_t ldp, int64_t split_stride,
 // Spectral-norm estimate (spectral.hip).  Y: my x bp binary64 (ldy, zero
 // columns up to bp); Z: split partials Z_s[row * bp + c] of nz rows (T).
 // The launcher sets gy, gz (workgroups per matrix) and the row ranges; part
-// holds (gy + gz) x 64 x 64 doubles.
+// holds (gy + gz + 2) x 64 x 64 doubles.
 constexpr int kMaxSpecWGs = 128;
 template <typename T>
 struct SpecGramArgs {
@@ -318,7 +318,7 @@ struct SpecGramArgs {
   int64_t rows_per_wg_y, rows_per_wg_z;
 };
 struct SpecFinishArgs {
-  const double* part; int gy, gz;
+  double* part; int gy, gz;    // partials, then room for their sums (2 x 64 x 64)
   DevState* st;
   double* trace; int block;    // trace[block] = estimate (block >= 0)
 };
@@ -329,8 +329,13 @@ hipError_t launch_spec_finish(const SpecFinishArgs& a, hipStream_t s);
 hipError_t launch_scaled_identity(double* Tm, int64_t ldt, const DevState* st, hipStream_t s);
 
 // GaLore subspace map (map.hip): out = (Q_new^T Q_old) M with split-K
-// partials Cpart (nsplit x r_new x r_old) and C (r_new x r_old).
+// partials Cpart (nsplit matrices of map_c_elems values) and C (one more),
+// each C^T with its r_new columns padded to kMapPad values.
 constexpr int kMaxMapSplits = 16;
+constexpr int kMapPad = 16;
+inline int64_t map_c_elems(int64_t r_new, int64_t r_old) {
+  return round_up(r_old, kMapPad) * r_new;
+}
 int map_splits(int64_t r_new, int64_t r_old, int64_t m, int num_cus);
 template <typename T>
 hipError_t launch_subspace_map(const T* Qnew, int64_t ldqn, int64_t r_new, const T* Qold,
