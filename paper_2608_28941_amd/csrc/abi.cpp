@@ -32,7 +32,11 @@ using namespace rrf;
 
 namespace {
 
-constexpr int kMaxUpdSplits = 8;
+// Column splits of an update (each takes one slab of the sample's partials):
+// 16 on panels of up to 32768 rows, whose few row blocks need them to fill the
+// device, 8 above.
+inline int max_upd_splits(int64_t m_max) { return m_max <= 32768 ? 16 : 8; }
+
 constexpr int kMaxRedSplits = 32;
 constexpr int kOmLd = 256;        // Omega stored [c][q]: a batch of 256 sketch columns
 constexpr int kPanelGrid = 0;      // column-by-column panel, one grid reduction per column
@@ -41,6 +45,7 @@ constexpr int kPanelGram = 2;      // column recurrence from the Gram matrix, on
 constexpr int kPanelAuto = 3;      // kPanelGram
 constexpr int kTLd = 64;          // T stored like geqrt's T: 64 rows
 constexpr double kLookaheadBytes = 512.0 * (1 << 20);   // largest matrix with look-ahead
+constexpr double kSmallBytes = 4.0 * (1 << 20);         // several blocks take 32 columns
 
 struct Sizes {
   int64_t ldb, kcap, kcols;
@@ -73,7 +78,7 @@ Sizes compute_sizes(rrf_dtype dt, int64_t m_max, int64_t n_max, int64_t b_max,
   z.V = (size_t)z.ldb * z.kcols * 8;
   z.Tm = (size_t)kTLd * z.kcols * 8;
   z.tau = (size_t)z.kcols * 8;
-  z.Ypart = (size_t)kMaxUpdSplits * z.ldb * 64 * e;
+  z.Ypart = (size_t)max_upd_splits(m_max) * z.ldb * 64 * e;
   z.ldysum = z.ldb + 2048;   // >= the panel grid's padded row count
   z.Ysum = (size_t)z.ldysum * 64 * 8;
   // Omega and W carry zero rows up to the next multiple of the update chunk.
@@ -84,10 +89,11 @@ Sizes compute_sizes(rrf_dtype dt, int64_t m_max, int64_t n_max, int64_t b_max,
   z.W = (size_t)(n_max + kUpdChunk) * kGroupMax * 8;
   z.Q = (size_t)z.ldb * std::max<int64_t>(z.kcap, 1) * e;
   z.Q64 = dt == RRF_F32 ? (size_t)z.ldb * std::max<int64_t>(z.kcap, 1) * 8 : 0;
-  z.normpart = (size_t)(ceil_div(m_max, kUpdRows) * kMaxUpdSplits + 1) * 2 * 8;
+  z.normpart = (size_t)(ceil_div(m_max, kUpdRows) * max_upd_splits(m_max) + 1) * 2 * 8;
   // The same partials as epoch-tagged words (two per value), when the
   // update's last workgroup finalizes.
-  z.normtag = z.normpart * 2;
+  // Then kMaxSuper block norms per column split, two words each.
+  z.normtag = z.normpart * 2 + (size_t)16 * kMaxSuper * 2 * 8;
   // Panel partials: two epoch-tagged 64-bit words per value.
   z.red = (size_t)2 * kMaxPanelWGs * 64 * 2 * 8;
   z.rowj = (size_t)2 * 64 * 2 * 8;
@@ -151,6 +157,8 @@ struct rrf_plan {
   DevState* st_host;
   DevState* st_mirror;   // st_host's device address (the finalisation's copy)
   int stop_mode, timing, panel_target;
+  int64_t t_blocks = 0;      // > 0: T of the last run still in sub-blocks of several
+                             // blocks of this width
   int log;                   // RRF_LOG=1: one stderr line per run, one per block
   int gram_fused_max;         // most workgroups of a Gram panel inside the update's launch
   int sub_max;                // widest sub-block (16, 32 or 64 columns; 0: 64)
@@ -210,10 +218,10 @@ void free_plan(rrf_plan* p) {
   delete p;
 }
 
-int upd_splits(int64_t mr, int64_t n, int num_cus) {
+int upd_splits(int64_t mr, int64_t n, int num_cus, int smax) {
   const int64_t row_wgs = ceil_div(mr, kUpdRows);
   int64_t s = ceil_div(4 * (int64_t)num_cus, std::max<int64_t>(row_wgs, 1));
-  s = std::min<int64_t>(s, kMaxUpdSplits);
+  s = std::min<int64_t>(s, smax);
   s = std::min<int64_t>(s, std::max<int64_t>(1, n / 256));
   return (int)std::max<int64_t>(s, 1);
 }
@@ -222,10 +230,12 @@ int upd_splits(int64_t mr, int64_t n, int num_cus) {
 // workgroup slots for most of the launch, and the update's workgroups run in
 // rounds over the free slots; the split count that minimises rounds x
 // columns per split avoids a nearly empty last round (fewest splits on ties:
-// less partial-sample traffic).
-int upd_splits_fused(int64_t mr, int64_t n, int64_t free_slots) {
+// less partial-sample traffic).  At least 512 columns per split: at 4096 x
+// 4096 fp32 more splits only slow the panel beside them (9.72 ms per run at
+// 512, 9.90 at 256, 11.8 at 1024).
+int upd_splits_fused(int64_t mr, int64_t n, int64_t free_slots, int split_max) {
   const int64_t row_wgs = std::max<int64_t>(ceil_div(mr, kUpdRows), 1);
-  const int64_t smax = std::max<int64_t>(1, std::min<int64_t>(kMaxUpdSplits, n / 256));
+  const int64_t smax = std::max<int64_t>(1, std::min<int64_t>(split_max, n / 512));
   const int64_t slots = std::max<int64_t>(free_slots, 1);
   int best = 1;
   double best_cost = 1e300;
@@ -492,6 +502,7 @@ void set_finalize(rrf_plan* p, UpdateArgs<T>& u, int nparts, int block, int64_t 
   f.nparts = nparts; f.st = p->st; f.mirror = p->st_mirror; f.tt = p->trace_trail_d; f.ts = p->trace_sub_d;
   f.block = block; f.k_after = k_after; f.k_cap = k_cap; f.mode = mode; f.tol = tol;
   f.init = init;
+  f.nblk = 1;
 }
 
 template <typename T>
@@ -511,11 +522,13 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   int64_t kcap = std::min(m, n);
   if (p->k_max > 0) kcap = std::min(kcap, p->k_max);
   const int mode = p->stop_mode;
+  const int usmax = max_upd_splits(p->m_max);
   p->trace_trail.clear();
   p->trace_sub.clear();
   p->sub_start.clear();
   p->spec.clear();
   p->nblocks = 0;
+  p->t_blocks = 0;
 
   // Blocks of b columns (the last one ragged at k_cap) run as sub-blocks of
   // at most 64 columns: Householder QR is column by column, so factoring a
@@ -525,9 +538,32 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   //
   int sub_max = mode == RRF_STOP_SPECTRAL ? kMaxBlock : p->sub_max;
   if (sub_max == 0) sub_max = kMaxBlock;
+  // Narrow blocks go the other way: a sub-block holds up to kMaxSuper whole
+  // blocks, whose stop tests then run in order behind one update (the trailing
+  // norms after the earlier blocks follow from the last one and the blocks'
+  // rows; finalize_state).  When one of them ends the run, the reflectors past
+  // it are dropped: they only touch rows past it.  A pass over B then serves
+  // up to 64 columns: 4096 x 4096 fp32, b = 32: 9.7 ms per run against 10.6;
+  // 131072 x 2048 fp64, b = 32: 10.2 against 11.7.  On matrices of at most
+  // 4 MiB up to 32 columns: there the panel is what a pass waits for, and wide
+  // panels form their Gram matrix more often (500 x 300 fp64, b = 16: 0.68 ms,
+  // 0.87 at 64 columns, 0.76 at 16).  Not with the spectral test, which needs
+  // every block's own updated matrix, nor with power iterations, whose sample
+  // does.
+  const int64_t super_cols =
+      std::min(sub_max, (double)m * (double)n * e <= kSmallBytes ? 32 : kMaxBlock);
+  // Only where the wider panel takes the Gram route: the tree of the tall-skinny
+  // QR has scratch for the plan's own block width alone, and a panel that the
+  // Gram route holds at the block's width stays on it.
+  int64_t per_sub =
+      mode == RRF_STOP_SPECTRAL || p->power > 0 || p->panel_mode != kPanelAuto
+          ? 1 : std::max<int64_t>(1, std::min<int64_t>(kMaxSuper, super_cols / b));
+  for (PanelShape shs; per_sub > 1; --per_sub)
+    if (gram_panel_shape(m, (int)std::min(per_sub * b, kcap), p->num_cus, &shs)) break;
+  const int64_t bs = per_sub * b;     // columns between host-side stop tests
   auto sub_width = [&](int64_t kk) -> int64_t {
     if (kk >= kcap) return 0;
-    const int64_t be = std::min((kk / b) * b + b, kcap);
+    const int64_t be = std::min((kk / bs) * bs + bs, kcap);
     return std::min<int64_t>(sub_max, be - kk);
   };
   // Work credited to a stage for the sub-block that starts at column col,
@@ -577,7 +613,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   u.Om = om_win; u.ldo = kOmLd; u.qp = q0; u.P = Yp; u.ldp = ldb;
   u.split_stride = ldb * 64; u.s0 = 0; u.normpart = p->normpart;
   {
-    const int su0 = upd_splits(m, n, p->num_cus);
+    const int su0 = upd_splits(m, n, p->num_cus, usmax);
     u.cols_per_split = round_up(ceil_div(n, su0), 2 * kUpdChunk);
   }
   int ysplits = (int)ceil_div(n, u.cols_per_split);
@@ -616,6 +652,11 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   const bool la_gram = alg0 == kPanelGram;
   bool la = p->lookahead != 0 && power == 0 && kcap > b0 && (alg0 == kPanelGrid || la_gram) &&
             (double)m * (double)n * e <= kLookaheadBytes;
+  // Blocks of more than 64 columns whose last sub-block is narrower (96: 64 and
+  // 32): the panel of one width does not run inside the update of the other,
+  // and the look-ahead without that only adds the redundant panel update
+  // (8169 x 461 fp32, b = 96: 1.41 ms with it, 1.18 without).
+  if (bs > sub_max && bs % sub_max != 0 && pad16(bs % sub_max) != pad16(sub_max)) la = false;
   // The shape of the look-ahead panel of a sub-block (mr rows, width bb).
   auto la_shape = [&](int64_t mr, int64_t bb, PanelShape* sh) -> bool {
     if (la_gram) return gram_fused_shape(mr, (int)bb, p->gram_fused_max, sh);
@@ -634,6 +675,9 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   bool w_ready = false;      // W of this sub-block was formed at the end of the last one
   bool w_gathered = false;   // ... together with its look-ahead gather
   double E_prev2 = 0.0;      // the stopping quantity one state read earlier
+  int64_t trim_from = 0, trim_to = 0;   // columns of the last sub-block past the final k
+  // Stages credited with the panel of this sub-block and the next one.
+  int last_panel_stage = RRF_STAGE_PANEL, next_panel_stage = RRF_STAGE_PANEL;
 
   // The look-ahead gather of the sample S that the panel of sub-block
   // kk + bb is factored from (sums of the split partials, slab rows from yo,
@@ -721,7 +765,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
       us.V = nullptr; us.ldv = 0; us.bp = 0; us.W = nullptr; us.ldw = 0;
       us.Om = (T*)p->W; us.ldo = bpp; us.qp = bpp; us.P = Yp; us.ldp = ldb;
       us.split_stride = ldb * 64; us.s0 = 0; us.normpart = nullptr;
-      us.cols_per_split = round_up(ceil_div(n, upd_splits(mpp, n, p->num_cus)), 2 * kUpdChunk);
+      us.cols_per_split = round_up(ceil_div(n, upd_splits(mpp, n, p->num_cus, usmax)), 2 * kUpdChunk);
       const int sus = (int)ceil_div(n, us.cols_per_split);
       const double uby = e * (mpp * n + mpp * bb);
       RRF_LAUNCH(p, RRF_STAGE_SAMPLE, fl, uby, launch_update<T>(us, sus, s));
@@ -770,12 +814,15 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     const int64_t mp = m - k;
     p->sub_start.push_back(k);
     const int64_t k_next = k + bi;
-    const bool at_end = k_next == kcap || k_next % b == 0;   // a stop test follows
+    const bool at_end = k_next == kcap || k_next % bs == 0;  // a stop test follows
     const int64_t b_next = sub_width(k_next);
     bool s1_done = false;      // sub-block 0: S_1 = A Omega_1 taken with the panel
+    last_panel_stage = next_panel_stage;
+    next_panel_stage = RRF_STAGE_PANEL;
     if (panel_ready) {
       panel_ready = false;
     } else {
+      last_panel_stage = RRF_STAGE_PANEL;
       PanelShape sh, shf;
       int route = panel_route(p, mp, (int)bi, &sh);
       if (route < 0) return RRF_ERR_SHAPE;
@@ -809,7 +856,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
         u1.Om = om_win;
         u1.qp = bp;
         u1.normpart = nullptr;
-        const int su1 = upd_splits_fused(m, n, (int64_t)occ0 * p->num_cus - sh.G);
+        const int su1 = upd_splits_fused(m, n, (int64_t)occ0 * p->num_cus - sh.G, usmax);
         u1.cols_per_split = round_up(ceil_div(n, su1), 2 * kUpdChunk);
         const int ys1 = (int)ceil_div(n, u1.cols_per_split);
         GramPanelArgs ga{};
@@ -818,6 +865,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
         ga.part = p->gx;
         ga.sums = p->gx + kGramPartWords;
         const double sfl = 2.0 * m * n * b_next, sby = e * (m * n + m * b_next);
+        last_panel_stage = RRF_STAGE_SAMPLE;
         RRF_LAUNCH(p, RRF_STAGE_SAMPLE, sfl + pflops, sby + 16.0 * mp * bi,
                    launch_update_gram<T>(u1, ys1, ga, sh, s));
         spec(RRF_STAGE_SAMPLE, k_next, sfl, sby);
@@ -924,11 +972,11 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     ua.P = Yp; ua.ldp = ldb; ua.split_stride = ldb * 64; ua.s0 = bi;
     ua.normpart = p->normpart;
     const bool fused = panel_ready && la_gram && update_gram_supported(bp, q_s, pan_shape);
-    int su0 = upd_splits(mp, n, p->num_cus);
+    int su0 = upd_splits(mp, n, p->num_cus, usmax);
     if (fused) {
       const int occ = update_gram_occupancy<T>(pan_shape, false);
       if (occ > 0)
-        su0 = upd_splits_fused(mp, n, (int64_t)occ * p->num_cus - pan_shape.G);
+        su0 = upd_splits_fused(mp, n, (int64_t)occ * p->num_cus - pan_shape.G, usmax);
     }
     ua.cols_per_split = round_up(ceil_div(n, su0), 2 * kUpdChunk);
     const int su = (int)ceil_div(n, ua.cols_per_split);
@@ -938,8 +986,14 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     // The stop test runs in the update's last workgroup, except where the
     // spectral estimate of the next block comes between them.
     const bool fin_in_update = !(mode == RRF_STOP_SPECTRAL && at_end && b_next > 0);
-    if (fin_in_update)
+    if (fin_in_update) {
       set_finalize(p, ua, nparts, at_end ? blk : -1, k_next, kcap, mode, tol, 0);
+      ua.fin.nblk = (int)(per_sub > 1 ? ceil_div(bi, b) : 1);
+      ua.fin.nsplit = su;
+      ua.fin.bw = b;
+      ua.fin.k0 = k;
+      ua.fin.sub = p->normtag + p->sz.normpart * 2 / 8;
+    }
     if (panel_ready) {
       pan.epoch_base = next_epoch(p);
       if (fused) {
@@ -951,6 +1005,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
                    2.0 * e * mp * n + pan_bytes,
                    launch_update_gram<T>(ua, su, ga, pan_shape, s));
         spec(RRF_STAGE_UPDATE, k_next, pan_flops, pan_bytes);
+        next_panel_stage = RRF_STAGE_UPDATE;
       } else {
         RRF_LAUNCH(p, RRF_STAGE_UPDATE, upd_flops, 2.0 * e * mp * n,
                    launch_update<T>(ua, su, s));
@@ -1057,8 +1112,17 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     }
     he = hipEventSynchronize(p->state_ev);
     if (he != hipSuccess) return hip_fail(he);
-    k = k_next;
-    ++blk;
+    stop = p->st_host->stop != 0;
+    // A stop inside the sub-block keeps the columns up to its block's end.
+    const int done = per_sub > 1 ? p->st_host->blocks : 1;
+    if (stop && k + done * b < k_next) {
+      trim_from = k + done * b;
+      trim_to = k_next;
+      k = trim_from;
+    } else {
+      k = k_next;
+    }
+    blk += done;
     ++sub;
     yoff = bi;
     ysplits = su;
@@ -1066,9 +1130,20 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     if (next_w) w_ready = true;
     if (p->st_host->barrier_err) return RRF_ERR_INTERNAL;
     if (p->st_host->nonfinite) return RRF_ERR_NONFINITE;
-    stop = p->st_host->stop != 0;
   }
   p->nblocks = blk;
+  p->t_blocks = per_sub > 1 ? b : 0;
+  if (trim_to > trim_from) {
+    // The dropped reflectors' share of the last sub-block is not credited.
+    const double mp = (double)(m - p->sub_start.back());
+    const double w = (double)(trim_to - trim_from), wl = (double)(trim_to - p->sub_start.back());
+    const double dn = (double)n;
+    const double kept = wl - w;
+    p->flops[RRF_STAGE_REDUCE] -= 2.0 * mp * dn * w;
+    p->flops[RRF_STAGE_FORMW] -= dn * (wl * wl - kept * kept);
+    p->flops[RRF_STAGE_UPDATE] -= 2.0 * mp * dn * w;
+    p->flops[last_panel_stage] -= panel_flops(mp, wl) - panel_flops(mp, kept);
+  }
 
   // Explicit Q = H_0 ... H_{k-1} [I_k; 0], backward over the sub-blocks, in
   // binary64 (float plans round the result once).  Adjacent sub-blocks are
@@ -1669,6 +1744,23 @@ rrf_status rrf_get_reflectors(rrf_plan_t plan, const void** V, int64_t* ldv,
     }
     hipError_t e = hipStreamSynchronize(plan->stream);
     if (e != hipSuccess) return hip_fail(e);
+  }
+  // Sub-blocks of several blocks: each block's T (a diagonal block of theirs)
+  // to the first rows of its columns.
+  if (plan->t_blocks > 0) {
+    for (size_t i = 0; i < plan->sub_start.size(); ++i) {
+      const int64_t ki = plan->sub_start[i];
+      const int64_t ke = i + 1 < plan->sub_start.size() ? plan->sub_start[i + 1] : plan->last_k;
+      const int64_t bw = plan->t_blocks;
+      for (int64_t c = ki + bw; c < ke; c += bw) {
+        hipError_t e = launch_lift_rows(plan->Tm + c * kTLd, kTLd, c - ki,
+                                        (int)std::min(bw, ke - c), plan->stream);
+        if (e != hipSuccess) return hip_fail(e);
+      }
+    }
+    hipError_t e = hipStreamSynchronize(plan->stream);
+    if (e != hipSuccess) return hip_fail(e);
+    plan->t_blocks = 0;
   }
   *V = plan->V;
   *ldv = plan->sz.ldb;

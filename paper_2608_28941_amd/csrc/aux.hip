@@ -38,6 +38,15 @@ __global__ void convert_kernel(const Ts* src, int64_t lds, Td* dst, int64_t ldd,
     dst[r + c * ldd] = (Td)src[r + c * lds];
 }
 
+// Rows [r0, r0 + b) of b columns to rows [0, b), one thread per column (b at
+// most 64; a row is read before a thread writes it or any row past it).
+__global__ __launch_bounds__(64) void lift_rows_kernel(double* T, int64_t ldt, int64_t r0, int b) {
+  const int c = (int)threadIdx.x;
+  if (c >= b) return;
+  double* t = T + c * ldt;
+  for (int i = 0; i < b; ++i) t[i] = t[r0 + i];
+}
+
 }  // namespace
 
 hipError_t launch_finalize(const double* normpart, int nparts, DevState* st,
@@ -86,5 +95,11 @@ template hipError_t launch_copy<float>(const float*, int64_t, float*, int64_t, i
 template hipError_t launch_copy<double>(const double*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<double, float>(const double*, int64_t, float*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<float, double>(const float*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
+
+hipError_t launch_lift_rows(double* T, int64_t ldt, int64_t r0, int b, hipStream_t s) {
+  if (b < 1 || b > 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(lift_rows_kernel, dim3(1), dim3(64), 0, s, T, ldt, r0, b);
+  return hipGetLastError();
+}
 
 }  // namespace rrf

@@ -56,7 +56,7 @@ __device__ __forceinline__ void finalize_sums(int nparts, Get&& get, double& blk
 // The run-state update (one thread).  The wait error is read through the
 // coherent path: another thread of this workgroup may have just set it.
 __device__ __forceinline__ void finalize_state(const FinalizeArgs& f, double blk,
-                                               double trail) {
+                                               double trail, const double* sub) {
   DevState* st = f.st;
   const int werr =
       __hip_atomic_load(&st->barrier_err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -71,7 +71,40 @@ __device__ __forceinline__ void finalize_state(const FinalizeArgs& f, double blk
     // The wait error is cleared by the host before the run (this step may
     // itself have waited).
     st->stop = st->nonfinite || werr || !(E0 > st->sigma2) || f.k_cap == 0;
+  } else if (f.nblk > 1) {
+    // Several blocks in one sub-block: later blocks' reflections leave the
+    // norm over the rows from a block's end on as it was, so the trailing norm
+    // after block i is the last one plus the later blocks' rows; the stop
+    // tests run in order.
+    double after[kMaxSuper];   // trailing norm after each block
+    double e = trail;
+#pragma unroll
+    for (int i = kMaxSuper - 1; i >= 0; --i) {
+      after[i] = e;
+      if (i < f.nblk) e += sub[i];
+    }
+    st->nonfinite = st->nonfinite || !isfinite(e);
+    double es = st->E_sub, et = trail;
+    bool stop = false;
+    int done = f.nblk;
+#pragma unroll
+    for (int i = 0; i < kMaxSuper; ++i) {
+      if (i >= f.nblk || stop) continue;
+      es = es - sub[i];
+      if (es < 0.0) es = 0.0;
+      et = after[i];
+      f.tt[f.block + i] = et;
+      f.ts[f.block + i] = es;
+      const int64_t ka = min(f.k0 + (i + 1) * f.bw, f.k_after);
+      stop = st->nonfinite || werr || !((f.mode == 0 ? et : es) > st->sigma2) || ka >= f.k_cap;
+      if (stop) done = i + 1;
+    }
+    st->E_sub = es;
+    st->E_trail = et;
+    st->stop = stop;
+    st->blocks = done;
   } else {
+    st->blocks = 1;
     double es = st->E_sub - blk;
     if (es < 0.0) es = 0.0;
     st->E_sub = es;
@@ -100,6 +133,7 @@ __device__ __forceinline__ void finalize_state(const FinalizeArgs& f, double blk
     h->barrier_err = werr;
     h->spin_limit = st->spin_limit;
     h->E_spec = st->E_spec;
+    h->blocks = st->blocks;
   }
 }
 
@@ -110,7 +144,7 @@ __device__ __forceinline__ void finalize_plain(const double* np, const FinalizeA
     x = np[2 * i + 0];
     y = np[2 * i + 1];
   }, blk, trail);
-  if (threadIdx.x == 0) finalize_state(f, blk, trail);
+  if (threadIdx.x == 0) finalize_state(f, blk, trail, nullptr);
 }
 
 // Finalize from epoch-tagged partials (4 words per part), waiting until every
@@ -134,7 +168,29 @@ __device__ __forceinline__ void finalize_tagged(const u64* nt, unsigned epoch,
     x = untag(w[0], w[1]);
     y = untag(w[2], w[3]);
   }, blk, trail);
-  if (threadIdx.x == 0) finalize_state(f, blk, trail);
+  // The blocks' own norms: the column splits' shares, added in split order.
+  __shared__ double sv[kMaxSuper][16];
+  double sub[kMaxSuper] = {};
+  if (f.nblk > 1) {   // uniform
+    for (int e = (int)threadIdx.x; e < kMaxSuper * f.nsplit; e += 256) {
+      const u64* q = f.sub + 2 * e;
+      u64 hi, lo;
+      unsigned spins = 0;
+      bool ok;
+      do {
+        hi = get_word(q);
+        lo = get_word(q + 1);
+        ok = tagged(hi, epoch) && tagged(lo, epoch);
+      } while ((!ok || forced) && keep_waiting(&spins, f.st));
+      sv[e % kMaxSuper][e / kMaxSuper] = untag(hi, lo);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+      for (int i = 0; i < kMaxSuper; ++i)
+        for (int s = 0; s < f.nsplit; ++s) sub[i] += sv[i][s];
+  }
+  if (threadIdx.x == 0) finalize_state(f, blk, trail, sub);
 }
 
 }  // namespace

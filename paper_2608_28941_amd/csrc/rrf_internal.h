@@ -23,6 +23,7 @@ constexpr int red_col_tiles(int bp) { return bp == 128 ? 1 : kRedCols / 64; }
 inline int64_t red_cols(int bp) { return 64 * red_col_tiles(bp); }
 constexpr int kRedRows = 32;       // rows per staged V chunk in the reduce
 constexpr int kRedChunk = 64;      // granularity of the reduce's row splits
+constexpr int kMaxSuper = 4;       // most blocks a sub-block holds
 constexpr int kPanelThreads = 256;
 constexpr int kMaxPanelWGs = 1024;
 
@@ -48,6 +49,8 @@ struct DevState {
   unsigned spin_limit;  // poll rounds before a grid-wide wait gives up; 0:
                         // every wait gives up at its first poll (tests)
   double E_spec;    // spectral-norm estimate of ||B[k:m, :]||_2^2 (spectral mode)
+  int blocks;       // blocks the last stop test went through (1, or up to
+                    // kMaxSuper of a sub-block that holds several)
 };
 
 // Launch descriptors -------------------------------------------------------
@@ -66,6 +69,12 @@ struct FinalizeArgs {
   int mode;
   double tol;
   int init;
+  // nblk > 1: the sub-block holds nblk blocks of bw columns (the last one
+  // ragged) from column k0 on; their rows' norms come tagged, kMaxSuper per
+  // column split (nsplit of them), at sub.
+  int nblk, nsplit;
+  int64_t bw, k0;
+  unsigned long long* sub;
 };
 
 template <typename T>
@@ -347,6 +356,8 @@ hipError_t launch_finalize(const double* normpart, int nparts, DevState* st,
                            DevState* mirror, double* trace_trail, double* trace_sub, int block,
                            int64_t k_after, int64_t k_cap, int mode,
                            double tol, int init, hipStream_t s);
+// Rows [r0, r0 + b) of b columns of T moved to rows [0, b).
+hipError_t launch_lift_rows(double* T, int64_t ldt, int64_t r0, int b, hipStream_t s);
 template <typename T>
 hipError_t launch_fill_identity(T* Q, int64_t ldq, int64_t m, int64_t k,
                                 hipStream_t s);

@@ -77,7 +77,7 @@ template <typename T, int BP, int QP>
 struct UpdLds {
   T wl[2][kUpdChunk * (BP > 0 ? BP + 1 : 1)];
   T ol[2][kUpdChunk * (QP > 0 ? QP + 1 : 1)];
-  double nred[2][4];
+  double nred[2 + kMaxSuper][4];
 };
 
 template <typename T, int BP, int QP, bool STORE>
@@ -103,9 +103,13 @@ __device__ __forceinline__ void update_body(UpdLds<T, BP, QP>& L, const UpdateAr
   const int64_t ce = min(a.n, cs + a.cols_per_split);
   // This workgroup's norm partials (thread 0's values): plain, or tagged with
   // the finalisation in the last update workgroup.
-  auto publish = [&](const double nbv, const double ntv) {
+  // sub: the blocks' own norms (thread i < kMaxSuper's values), from the
+  // workgroups of the first rows.
+  auto publish = [&](const double nbv, const double ntv, const double sub) {
     const int64_t wg = (int64_t)split * nrb + rb;
     if (a.normtag) {
+      if (a.fin.nblk > 1 && rb == 0 && threadIdx.x < kMaxSuper)
+        put_tagged(&a.fin.sub[2 * ((int64_t)split * kMaxSuper + threadIdx.x)], sub, a.fin_epoch);
       if (threadIdx.x == 0) {
         put_tagged(&a.normtag[4 * wg], nbv, a.fin_epoch);
         put_tagged(&a.normtag[4 * wg + 2], ntv, a.fin_epoch);
@@ -117,7 +121,7 @@ __device__ __forceinline__ void update_body(UpdLds<T, BP, QP>& L, const UpdateAr
     }
   };
   if (cs >= ce) {          // empty split (uniform per workgroup, before any barrier)
-    if (a.normpart) publish(0.0, 0.0);
+    if (a.normpart) publish(0.0, 0.0, 0.0);
     return;
   }
   int64_t r[RT];
@@ -352,9 +356,24 @@ __device__ __forceinline__ void update_body(UpdLds<T, BP, QP>& L, const UpdateAr
       nred[0][wave] = nb;
       nred[1][wave] = nt;
     }
+    const bool several = a.normtag && a.fin.nblk > 1 && rb == 0;   // uniform
+    if (several) {
+#pragma unroll
+      for (int i = 0; i < kMaxSuper; ++i) {
+        double v = 0.0;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          if (r[rt] < a.s0 && r[rt] >= i * a.fin.bw && r[rt] < (i + 1) * a.fin.bw) v += nq[rt];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) nred[2 + i][wave] = v;
+      }
+    }
     __syncthreads();
+    const int si = 2 + (int)(threadIdx.x % kMaxSuper);
     publish(((nred[0][0] + nred[0][1]) + nred[0][2]) + nred[0][3],
-            ((nred[1][0] + nred[1][1]) + nred[1][2]) + nred[1][3]);
+            ((nred[1][0] + nred[1][1]) + nred[1][2]) + nred[1][3],
+            several ? ((nred[si][0] + nred[si][1]) + nred[si][2]) + nred[si][3] : 0.0);
   }
 }
 
