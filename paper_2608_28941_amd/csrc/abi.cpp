@@ -44,6 +44,8 @@ constexpr int kPanelTsqr = 1;      // tall-skinny QR + Householder reconstructio
 constexpr int kPanelGram = 2;      // column recurrence from the Gram matrix, one exchange per sweep
 constexpr int kPanelAuto = 3;      // kPanelGram
 constexpr int kTLd = 64;          // T stored like geqrt's T: 64 rows
+constexpr size_t kStateBytes = 256;                     // pinned: state, then traces
+static_assert(sizeof(DevState) <= kStateBytes, "the traces follow the state");
 constexpr double kLookaheadBytes = 512.0 * (1 << 20);   // largest matrix with look-ahead
 constexpr double kSmallBytes = 4.0 * (1 << 20);         // several blocks take 32 columns
 
@@ -156,6 +158,9 @@ struct rrf_plan {
   DevState* st;
   DevState* st_host;
   DevState* st_mirror;   // st_host's device address (the finalisation's copy)
+  double *trace_h, *trace_hd;   // the traces behind st_host (host, device address)
+  OrgqrGroup* groups_hd;        // groups_h's device address
+  size_t trace_stride() const { return sz.trace / 3 / sizeof(double); }
   int stop_mode, timing, panel_target;
   int64_t t_blocks = 0;      // > 0: T of the last run still in sub-blocks of several
                              // blocks of this width
@@ -622,7 +627,8 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   set_finalize(p, u, nparts, -1, 0, kcap, mode, tol, 1);
   RRF_LAUNCH(p, RRF_STAGE_SAMPLE, 2.0 * m * n * b0, e * (m * n + m * b0),
              launch_update<T>(u, ysplits, s));
-  hipError_t he = read_state(p);
+  // (The finalisation has written the state into st_host.)
+  hipError_t he = hipStreamSynchronize(s);
   if (he != hipSuccess) return hip_fail(he);
   if (p->st_host->barrier_err) return RRF_ERR_INTERNAL;
   if (p->st_host->nonfinite) return RRF_ERR_NONFINITE;
@@ -1153,10 +1159,21 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   const int nsub = (int)p->sub_start.size();
   if (k > 0) {
     double* Qd = std::is_same<T, double>::value ? (double*)Q : (double*)p->Q64;
-    RRF_LAUNCH(p, RRF_STAGE_ORGQR, 0.0, 8.0 * m * k,
-               launch_fill_identity<double>(Qd, ldb, m, k, s));
     // gi: index into the group list (merged T in Tp), or -1 (one block, its
     // own T).
+    // [I_k; 0], and the group list (ng groups) from its pinned staging in the
+    // same launch: a copy queued in the stream took 20 us before the next
+    // kernel started.
+    bool filled = false;
+    auto fill = [&](int ng) {
+      he = ev_mark(p, RRF_STAGE_ORGQR, s);
+      if (he == hipSuccess)
+        he = launch_fill_identity<double>(Qd, ldb, m, k, p->groups_hd, p->groups_d,
+                                          ng * sizeof(OrgqrGroup), s);
+      if (he == hipSuccess) he = ev_mark(p, RRF_STAGE_ORGQR, s);
+      p->launches[RRF_STAGE_ORGQR] += 1;
+      p->bytes[RRF_STAGE_ORGQR] += 8.0 * m * k;
+    };
     struct Pass { int64_t k0, b; int gi; };
     std::vector<Pass> passes;
     int ngroups = 0;
@@ -1215,23 +1232,37 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
         passes.swap(single);
         ngroups = 0;
       } else {
-        he = hipMemcpyAsync(p->groups_d, p->groups_h, ngroups * sizeof(OrgqrGroup),
-                            hipMemcpyHostToDevice, s);
+        fill(ngroups);
         if (he != hipSuccess) return hip_fail(he);
+        filled = true;
         GroupArgs ga{};
         ga.groups = p->groups_d; ga.ngroups = ngroups;
         ga.V = V; ga.ldv = ldb; ga.m = m;
         ga.Tm = Tm; ga.ldt = kTLd; ga.Tg = p->Tp; ga.ldg = kGroupMax;
         ga.part = (double*)p->Zpart;
+        ga.aligned = true;
+        for (int gi = 0; gi < ngroups; ++gi)
+          for (int c = 0; c < p->groups_h[gi].nb; ++c)
+            ga.aligned = ga.aligned && p->groups_h[gi].off[c] % 16 == 0;
         // About two workgroups per compute unit over all groups (each split is
-        // a chain of 32-row chunks), splits of at least 256 rows.
+        // a chain of 32-row chunks), splits of at least 256 rows; of 64 rows
+        // where that still leaves less than a workgroup per compute unit (500
+        // rows, 2 groups: 43 us with 2 splits, 16 with 8).
         ga.nsplit = (int)std::max<int64_t>(
-            1, std::min<int64_t>({ceil_div(gram_rows, 256),
-                                  std::max<int64_t>(64, ceil_div(2 * (int64_t)p->num_cus, ngroups)),
-                                  cap}));
+            1, std::min<int64_t>(
+                   cap, std::max<int64_t>(
+                            std::min<int64_t>(
+                                ceil_div(gram_rows, 256),
+                                std::max<int64_t>(64, ceil_div(2 * (int64_t)p->num_cus, ngroups))),
+                            std::min<int64_t>(ceil_div(gram_rows, 64),
+                                              ceil_div((int64_t)p->num_cus, ngroups)))));
         RRF_LAUNCH(p, RRF_STAGE_ORGQR, 2.0 * gram_rows * ent * ngroups,
                    8.0 * gram_rows * kGroupMax * ngroups, launch_orgqr_groups(ga, s));
       }
+    }
+    if (!filled) {
+      fill(0);
+      if (he != hipSuccess) return hip_fail(he);
     }
     for (const Pass& ps : passes) {
       const int64_t ki = ps.k0, bi = ps.b;
@@ -1259,13 +1290,19 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
       RRF_LAUNCH(p, RRF_STAGE_ORGQR, 0.0, 12.0 * m * k,
                  (launch_convert<double, float>(Qd, ldb, (float*)Q, ldb, m, k, s)));
   }
+  // The final state (errors recorded after the last state read: the thin
+  // kernel's grid exchange in the explicit-Q pass) and the trace go to pinned
+  // host memory in one launch, and the host waits once.  The estimate exists
+  // for the blocks that ended below the cap, and only in spectral mode.
+  const int nspec = mode == RRF_STOP_SPECTRAL ? (k < kcap ? blk : blk - 1) : 0;
+  if (k > 0) {
+    he = launch_export(p->st, p->st_mirror, p->trace_trail_d, p->trace_sub_d, p->trace_spec_d,
+                       blk, nspec, p->trace_hd, p->trace_stride(), s);
+    if (he != hipSuccess) return hip_fail(he);
+  }
   he = hipStreamSynchronize(s);
   if (he != hipSuccess) return hip_fail(he);
   if (k > 0) {
-    // Errors recorded after the last state read: the thin kernel's grid
-    // exchange (last sub-block of Q).
-    he = read_state(p);
-    if (he != hipSuccess) return hip_fail(he);
     if (p->st_host->barrier_err) return RRF_ERR_INTERNAL;
     if (p->st_host->nonfinite) return RRF_ERR_NONFINITE;
   }
@@ -1276,23 +1313,13 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     p->bytes[w.stage] -= w.bytes;
   }
 
-  // Trace back to the host.
   if (blk > 0) {
-    p->trace_trail.resize(blk);
-    p->trace_sub.resize(blk);
+    const double* th = p->trace_h;
+    const size_t ts = p->trace_stride();
+    p->trace_trail.assign(th, th + blk);
+    p->trace_sub.assign(th + ts, th + ts + blk);
     p->trace_spec.assign(blk, std::nan(""));
-    he = hipMemcpy(p->trace_trail.data(), p->trace_trail_d, blk * sizeof(double),
-                   hipMemcpyDeviceToHost);
-    if (he == hipSuccess)
-      he = hipMemcpy(p->trace_sub.data(), p->trace_sub_d, blk * sizeof(double),
-                     hipMemcpyDeviceToHost);
-    // The estimate exists for the blocks that ended below the cap, and only
-    // in spectral mode.
-    const int nspec = mode == RRF_STOP_SPECTRAL ? (k < kcap ? blk : blk - 1) : 0;
-    if (he == hipSuccess && nspec > 0)
-      he = hipMemcpy(p->trace_spec.data(), p->trace_spec_d, nspec * sizeof(double),
-                     hipMemcpyDeviceToHost);
-    if (he != hipSuccess) return hip_fail(he);
+    std::copy(th + 2 * ts, th + 2 * ts + nspec, p->trace_spec.begin());
   }
   p->E0 = p->st_host->E0;
   p->sigma2 = p->st_host->sigma2;
@@ -1561,12 +1588,18 @@ rrf_status plan_create(rrf_plan_t* plan, int dtype_bits, int64_t m_max, int64_t 
     ++counter;
     const char* f = std::getenv("RRF_FAULT_ALLOC");
     if (f && std::atoi(f) == counter) e = hipErrorOutOfMemory;
-    else e = hipHostMalloc((void**)&p->st_host, sizeof(DevState),
+    else e = hipHostMalloc((void**)&p->st_host, kStateBytes + p->sz.trace,
                            hipHostMallocMapped | hipHostMallocCoherent);
   }
   // The stop test writes its decision straight into st_host.
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&p->st_mirror, p->st_host, 0);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&p->groups_h, p->sz.groups, 0);
+  if (e == hipSuccess) {
+    p->trace_h = reinterpret_cast<double*>(reinterpret_cast<char*>(p->st_host) + kStateBytes);
+    p->trace_hd = reinterpret_cast<double*>(reinterpret_cast<char*>(p->st_mirror) + kStateBytes);
+    e = hipHostMalloc((void**)&p->groups_h, p->sz.groups,
+                      hipHostMallocMapped | hipHostMallocCoherent);
+  }
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&p->groups_hd, p->groups_h, 0);
   if (e == hipSuccess) e = hipMemsetAsync(p->red, 0, p->sz.red, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->rowj, 0, p->sz.rowj, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(p->gx, 0, p->sz.gx, p->stream);

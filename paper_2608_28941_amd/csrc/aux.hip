@@ -12,8 +12,12 @@ __global__ __launch_bounds__(256) void finalize_kernel(const double* np, Finaliz
   finalize_plain(np, f);
 }
 
+// [I; 0], and nw words from gsrc to gdst (the first workgroup).
 template <typename T>
-__global__ void fill_identity_kernel(T* Q, int64_t ldq, int64_t m, int64_t k) {
+__global__ void fill_identity_kernel(T* Q, int64_t ldq, int64_t m, int64_t k,
+                                     const unsigned* gsrc, unsigned* gdst, int nw) {
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = (int)threadIdx.x; i < nw; i += (int)blockDim.x) gdst[i] = gsrc[i];
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= m) return;
   for (int64_t c = blockIdx.y; c < k; c += gridDim.y)
@@ -36,6 +40,24 @@ __global__ void convert_kernel(const Ts* src, int64_t lds, Td* dst, int64_t ldd,
   if (r >= rows) return;
   for (int64_t c = blockIdx.y; c < cols; c += gridDim.y)
     dst[r + c * ldd] = (Td)src[r + c * lds];
+}
+
+// The run state and the traces (blk blocks, the estimates of nspec) to pinned
+// host memory.
+__global__ __launch_bounds__(256) void export_kernel(const DevState* st, DevState* h,
+                                                     const double* tt, const double* ts,
+                                                     const double* tp, int blk, int nspec,
+                                                     double* th, size_t stride) {
+  if (threadIdx.x == 0) {
+    DevState v = *st;
+    v.barrier_err = __hip_atomic_load(&st->barrier_err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *h = v;
+  }
+  for (int i = (int)threadIdx.x; i < blk; i += 256) {
+    th[i] = tt[i];
+    th[stride + i] = ts[i];
+    if (i < nspec) th[2 * stride + i] = tp[i];
+  }
 }
 
 // Rows [r0, r0 + b) of b columns to rows [0, b), one thread per column (b at
@@ -61,11 +83,12 @@ hipError_t launch_finalize(const double* normpart, int nparts, DevState* st,
 }
 
 template <typename T>
-hipError_t launch_fill_identity(T* Q, int64_t ldq, int64_t m, int64_t k,
-                                hipStream_t s) {
+hipError_t launch_fill_identity(T* Q, int64_t ldq, int64_t m, int64_t k, const void* gsrc,
+                                void* gdst, size_t gbytes, hipStream_t s) {
   if (m <= 0 || k <= 0) return hipSuccess;
   dim3 grid((unsigned)ceil_div(m, 256), (unsigned)(k < 4096 ? k : 4096));
-  hipLaunchKernelGGL(fill_identity_kernel<T>, grid, dim3(256), 0, s, Q, ldq, m, k);
+  hipLaunchKernelGGL(fill_identity_kernel<T>, grid, dim3(256), 0, s, Q, ldq, m, k,
+                     (const unsigned*)gsrc, (unsigned*)gdst, (int)(gbytes / 4));
   return hipGetLastError();
 }
 
@@ -89,12 +112,19 @@ hipError_t launch_convert(const Ts* src, int64_t lds, Td* dst, int64_t ldd,
   return hipGetLastError();
 }
 
-template hipError_t launch_fill_identity<float>(float*, int64_t, int64_t, int64_t, hipStream_t);
-template hipError_t launch_fill_identity<double>(double*, int64_t, int64_t, int64_t, hipStream_t);
+template hipError_t launch_fill_identity<double>(double*, int64_t, int64_t, int64_t, const void*, void*, size_t, hipStream_t);
 template hipError_t launch_copy<float>(const float*, int64_t, float*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_copy<double>(const double*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<double, float>(const double*, int64_t, float*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<float, double>(const float*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
+
+hipError_t launch_export(const DevState* st, DevState* h, const double* tt, const double* ts,
+                         const double* tp, int blk, int nspec, double* th, size_t stride,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(export_kernel, dim3(1), dim3(256), 0, s, st, h, tt, ts, tp, blk, nspec, th,
+                     stride);
+  return hipGetLastError();
+}
 
 hipError_t launch_lift_rows(double* T, int64_t ldt, int64_t r0, int b, hipStream_t s) {
   if (b < 1 || b > 64) return hipErrorInvalidValue;

@@ -266,6 +266,7 @@ struct GroupArgs {
   const double* Tm; int64_t ldt;
   double* Tg; int64_t ldg;
   double* part; int nsplit;
+  bool aligned;                // every block of every group starts at a multiple of 16
 };
 hipError_t launch_orgqr_groups(const GroupArgs& a, hipStream_t s);
 
@@ -358,9 +359,15 @@ hipError_t launch_finalize(const double* normpart, int nparts, DevState* st,
                            double tol, int init, hipStream_t s);
 // Rows [r0, r0 + b) of b columns of T moved to rows [0, b).
 hipError_t launch_lift_rows(double* T, int64_t ldt, int64_t r0, int b, hipStream_t s);
+// Q = [I_k; 0], and gbytes (whole words) from gsrc to gdst.
 template <typename T>
-hipError_t launch_fill_identity(T* Q, int64_t ldq, int64_t m, int64_t k,
-                                hipStream_t s);
+hipError_t launch_fill_identity(T* Q, int64_t ldq, int64_t m, int64_t k, const void* gsrc,
+                                void* gdst, size_t gbytes, hipStream_t s);
+// *h = *st and, at th, th + stride, th + 2 stride, the traces tt, ts (blk
+// values) and tp (nspec values); h and th are pinned host memory.
+hipError_t launch_export(const DevState* st, DevState* h, const double* tt, const double* ts,
+                         const double* tp, int blk, int nspec, double* th, size_t stride,
+                         hipStream_t s);
 template <typename T>
 hipError_t launch_copy(const T* src, int64_t lds, T* dst, int64_t ldd,
                        int64_t rows, int64_t cols, hipStream_t s);
