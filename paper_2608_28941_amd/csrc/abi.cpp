@@ -1344,22 +1344,6 @@ int enum_bits(const E& e) {
 bool valid_dtype(int d) { return d == RRF_F32 || d == RRF_F64; }
 
 template <typename T>
-hipError_t to_plan_type(const double* src, int64_t lds, T* dst, int64_t ldd,
-                        int64_t rows, int64_t cols, hipStream_t s) {
-  if (std::is_same<T, double>::value)
-    return launch_copy<double>(src, lds, (double*)dst, ldd, rows, cols, s);
-  return launch_convert<double, float>(src, lds, (float*)dst, ldd, rows, cols, s);
-}
-
-template <typename T>
-hipError_t from_plan_type(const T* src, int64_t lds, double* dst, int64_t ldd,
-                          int64_t rows, int64_t cols, hipStream_t s) {
-  if (std::is_same<T, double>::value)
-    return launch_copy<double>((const double*)src, lds, dst, ldd, rows, cols, s);
-  return launch_convert<float, double>((const float*)src, lds, dst, ldd, rows, cols, s);
-}
-
-template <typename T>
 rrf_status panel_stage(rrf_plan* p, const T* Y, int64_t m, int64_t b,
                        int64_t ldy, T* Vout, int64_t ldv, T* Tout, int64_t ldt,
                        T* tauout) {
@@ -1379,11 +1363,12 @@ rrf_status panel_stage(rrf_plan* p, const T* Y, int64_t m, int64_t b,
   pa.Tm = p->Tm; pa.ldt = kTLd; pa.tau = p->tau;
   pa.red = p->red; pa.rowj = p->rowj; pa.st = p->st; pa.G = sh.G;
   e = run_panel(p, pa, route, sh, s);
-  if (e == hipSuccess) e = to_plan_type<T>(p->V, p->sz.ldb, Vout, ldv, m, b, s);
-  if (e == hipSuccess) e = to_plan_type<T>(p->Tm, kTLd, Tout, ldt, b, b, s);
-  if (e == hipSuccess) e = to_plan_type<T>(p->tau, 1, tauout, 1, b, 1, s);
-  // A grid-wide wait that gave up leaves V, T and tau undefined.
-  if (e == hipSuccess) e = read_state(p);
+  // V, T, tau and the run state leave in one launch.  A grid-wide wait that
+  // gave up leaves V, T and tau undefined.
+  if (e == hipSuccess)
+    e = launch_panel_out<T>(p->V, p->sz.ldb, p->Tm, p->tau, m, (int)b, Vout, ldv, Tout, ldt,
+                            tauout, p->st, p->st_mirror, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e);
   return p->st_host->barrier_err ? RRF_ERR_INTERNAL : RRF_OK;
 }
@@ -1398,10 +1383,7 @@ rrf_status larfb_stage(rrf_plan* p, int trans, const T* V, int64_t ldv,
   double* Vw = p->V;
   double* Tw = p->Tm;
   // Zero-padded binary64 copies of V (m x bp) and T (bp x bp).
-  hipError_t e = hipMemsetAsync(Vw, 0, (size_t)ldb * bp * sizeof(double), s);
-  if (e == hipSuccess) e = hipMemsetAsync(Tw, 0, (size_t)kTLd * bp * sizeof(double), s);
-  if (e == hipSuccess) e = from_plan_type<T>(V, ldv, Vw, ldb, m, b, s);
-  if (e == hipSuccess) e = from_plan_type<T>(Tm, ldt, Tw, kTLd, b, b, s);
+  hipError_t e = launch_reflector_in<T>(V, ldv, Tm, ldt, m, (int)b, bp, Vw, ldb, Tw, s);
   if (e != hipSuccess) return hip_fail(e);
   stats_reset(p);
   if (std::is_same<T, double>::value && n <= 64) {

@@ -42,6 +42,40 @@ __global__ void convert_kernel(const Ts* src, int64_t lds, Td* dst, int64_t ldd,
     dst[r + c * ldd] = (Td)src[r + c * lds];
 }
 
+// A caller's reflector to the plan's binary64 V (m x bp) and T (64 rows, bp
+// columns), zero past its b columns, in one launch (grid rows x bp).
+template <typename T>
+__global__ __launch_bounds__(256) void reflector_in_kernel(const T* V, int64_t ldv, const T* Tm,
+                                                           int64_t ldt, int64_t m, int b,
+                                                           double* Vw, int64_t ldw, double* Tw) {
+  const int c = (int)blockIdx.y;
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (r < m) Vw[r + c * ldw] = c < b ? (double)V[r + (int64_t)min(c, b - 1) * ldv] : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    const int i = (int)threadIdx.x;
+    Tw[i + c * 64] = (i < b && c < b) ? (double)Tm[i + (int64_t)c * ldt] : 0.0;
+  }
+}
+
+// A factored panel to the caller's V (m x b), T (b x b) and tau, and the run
+// state to its pinned copy, in one launch (grid rows x b).
+template <typename T>
+__global__ __launch_bounds__(256) void panel_out_kernel(const double* Vw, int64_t ldw,
+                                                        const double* Tw, const double* tauw,
+                                                        int64_t m, int b, T* V, int64_t ldv,
+                                                        T* Tm, int64_t ldt, T* tau,
+                                                        const DevState* st, DevState* h) {
+  const int c = (int)blockIdx.y;
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (r < m) V[r + c * ldv] = (T)Vw[r + c * ldw];
+  if (blockIdx.x == 0) {
+    const int i = (int)threadIdx.x;
+    if (i < b) Tm[i + c * ldt] = (T)Tw[i + c * 64];
+    if (i == 0) tau[c] = (T)tauw[c];
+    if (c == 0 && i == 0) *h = *st;
+  }
+}
+
 // The run state and the traces (blk blocks, the estimates of nspec) to pinned
 // host memory.
 __global__ __launch_bounds__(256) void export_kernel(const DevState* st, DevState* h,
@@ -117,6 +151,29 @@ template hipError_t launch_copy<float>(const float*, int64_t, float*, int64_t, i
 template hipError_t launch_copy<double>(const double*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<double, float>(const double*, int64_t, float*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<float, double>(const float*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
+
+template <typename T>
+hipError_t launch_reflector_in(const T* V, int64_t ldv, const T* Tm, int64_t ldt, int64_t m,
+                               int b, int bp, double* Vw, int64_t ldw, double* Tw,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(reflector_in_kernel<T>, dim3((unsigned)ceil_div(m, 256), (unsigned)bp),
+                     dim3(256), 0, s, V, ldv, Tm, ldt, m, b, Vw, ldw, Tw);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_panel_out(const double* Vw, int64_t ldw, const double* Tw, const double* tauw,
+                            int64_t m, int b, T* V, int64_t ldv, T* Tm, int64_t ldt, T* tau,
+                            const DevState* st, DevState* h, hipStream_t s) {
+  hipLaunchKernelGGL(panel_out_kernel<T>, dim3((unsigned)ceil_div(m, 256), (unsigned)b),
+                     dim3(256), 0, s, Vw, ldw, Tw, tauw, m, b, V, ldv, Tm, ldt, tau, st, h);
+  return hipGetLastError();
+}
+
+template hipError_t launch_reflector_in<float>(const float*, int64_t, const float*, int64_t, int64_t, int, int, double*, int64_t, double*, hipStream_t);
+template hipError_t launch_reflector_in<double>(const double*, int64_t, const double*, int64_t, int64_t, int, int, double*, int64_t, double*, hipStream_t);
+template hipError_t launch_panel_out<float>(const double*, int64_t, const double*, const double*, int64_t, int, float*, int64_t, float*, int64_t, float*, const DevState*, DevState*, hipStream_t);
+template hipError_t launch_panel_out<double>(const double*, int64_t, const double*, const double*, int64_t, int, double*, int64_t, double*, int64_t, double*, const DevState*, DevState*, hipStream_t);
 
 hipError_t launch_export(const DevState* st, DevState* h, const double* tt, const double* ts,
                          const double* tp, int blk, int nspec, double* th, size_t stride,

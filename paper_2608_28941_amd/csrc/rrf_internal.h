@@ -357,6 +357,18 @@ hipError_t launch_finalize(const double* normpart, int nparts, DevState* st,
                            DevState* mirror, double* trace_trail, double* trace_sub, int block,
                            int64_t k_after, int64_t k_cap, int mode,
                            double tol, int init, hipStream_t s);
+// A caller's V (m x b) and T to binary64 V (m x bp, ldw) and T (64 x bp), zero
+// past column b.
+template <typename T>
+hipError_t launch_reflector_in(const T* V, int64_t ldv, const T* Tm, int64_t ldt, int64_t m,
+                               int b, int bp, double* Vw, int64_t ldw, double* Tw,
+                               hipStream_t s);
+// A factored panel (V m x b, T 64 rows, tau) to the caller's arrays, and the
+// run state to its pinned copy h.
+template <typename T>
+hipError_t launch_panel_out(const double* Vw, int64_t ldw, const double* Tw, const double* tauw,
+                            int64_t m, int b, T* V, int64_t ldv, T* Tm, int64_t ldt, T* tau,
+                            const DevState* st, DevState* h, hipStream_t s);
 // Rows [r0, r0 + b) of b columns of T moved to rows [0, b).
 hipError_t launch_lift_rows(double* T, int64_t ldt, int64_t r0, int b, hipStream_t s);
 // Q = [I_k; 0], and gbytes (whole words) from gsrc to gdst.
