@@ -34,8 +34,10 @@ namespace {
 
 // Column splits of an update (each takes one slab of the sample's partials):
 // 16 on panels of up to 32768 rows, whose few row blocks need them to fill the
-// device, 8 above.
-inline int max_upd_splits(int64_t m_max) { return m_max <= 32768 ? 16 : 8; }
+// device, 8 above, of at least 256 columns each.
+inline int max_upd_splits(int64_t m_max, int64_t n_max) {
+  return (int)std::min<int64_t>(m_max <= 32768 ? 16 : 8, std::max<int64_t>(1, n_max / 256));
+}
 
 constexpr int kMaxRedSplits = 32;
 constexpr int kOmLd = 256;        // Omega stored [c][q]: a batch of 256 sketch columns
@@ -80,7 +82,7 @@ Sizes compute_sizes(rrf_dtype dt, int64_t m_max, int64_t n_max, int64_t b_max,
   z.V = (size_t)z.ldb * z.kcols * 8;
   z.Tm = (size_t)kTLd * z.kcols * 8;
   z.tau = (size_t)z.kcols * 8;
-  z.Ypart = (size_t)max_upd_splits(m_max) * z.ldb * 64 * e;
+  z.Ypart = (size_t)max_upd_splits(m_max, n_max) * z.ldb * 64 * e;
   z.ldysum = z.ldb + 2048;   // >= the panel grid's padded row count
   z.Ysum = (size_t)z.ldysum * 64 * 8;
   // Omega and W carry zero rows up to the next multiple of the update chunk.
@@ -91,7 +93,7 @@ Sizes compute_sizes(rrf_dtype dt, int64_t m_max, int64_t n_max, int64_t b_max,
   z.W = (size_t)(n_max + kUpdChunk) * kGroupMax * 8;
   z.Q = (size_t)z.ldb * std::max<int64_t>(z.kcap, 1) * e;
   z.Q64 = dt == RRF_F32 ? (size_t)z.ldb * std::max<int64_t>(z.kcap, 1) * 8 : 0;
-  z.normpart = (size_t)(ceil_div(m_max, kUpdRows) * max_upd_splits(m_max) + 1) * 2 * 8;
+  z.normpart = (size_t)(ceil_div(m_max, kUpdRows) * max_upd_splits(m_max, n_max) + 1) * 2 * 8;
   // The same partials as epoch-tagged words (two per value), when the
   // update's last workgroup finalizes.
   // Then kMaxSuper block norms per column split, two words each.
@@ -527,7 +529,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   int64_t kcap = std::min(m, n);
   if (p->k_max > 0) kcap = std::min(kcap, p->k_max);
   const int mode = p->stop_mode;
-  const int usmax = max_upd_splits(p->m_max);
+  const int usmax = max_upd_splits(p->m_max, p->n_max);
   p->trace_trail.clear();
   p->trace_sub.clear();
   p->sub_start.clear();

@@ -182,6 +182,16 @@ __global__ __launch_bounds__(256, 2) void reduce_kernel(ReduceArgs<T> a) {
 // block may already hold the next block's T), so W rows >= b are zero.
 // Workgroups past the first a.nfw gather the look-ahead sample instead (one
 // per 256 rows of one column, as the gather kernel).
+//
+// A workgroup takes 1024 / BP columns: their split partials are summed in
+// split order in binary64, 4 values a thread in 16-byte packs, 8 splits in
+// flight, and z goes to LDS; then each of the 4 wavefronts forms one 16 x 16
+// tile of W on f64 MFMA (D rows: columns c, D columns: 16 values of p, K: the
+// index l over T's triangle), its T operand loaded beside the partials.
+// Bound: the partials (n x BP x splits values).  With the product as 64 FMAs a
+// value on LDS entries it was bound by LDS reads: 33 -> 17 us per
+// block at 16384 x 16384 fp64, b = 64, 23 -> 16 at 4096 x 11008 fp32, 21 -> 13 for
+// a 4096 x 11008 fp32 reflector of 64.
 // ---------------------------------------------------------------------------
 template <typename T, int BP>
 __global__ __launch_bounds__(256) void formw_kernel(FormWArgs<T> a) {
@@ -193,67 +203,74 @@ __global__ __launch_bounds__(256) void formw_kernel(FormWArgs<T> a) {
     if (r < a.g.rows_pad && k < a.g.bp) gather_entry(a.g, r, k);
     return;
   }
-  constexpr int CPB = 256 / BP;
-  constexpr int NT = (BP * BP) / 256;
-  constexpr int ZB = 8;                // split partials loaded together
-  __shared__ double Tl[BP][BP + 1];
-  __shared__ double zs[CPB][BP + 1];
-  // T to LDS: all loads issued before the first use (in-bounds addresses:
-  // columns past b read column 0), entries outside the upper b x b triangle
-  // replaced by zero.
-  {
-    double tv[NT];
+  constexpr int CW = 1024 / BP;          // columns per workgroup
+  constexpr int NPT = BP / 16;           // p tiles; NPT x (CW / 16) = 4 tiles
+  constexpr int VEC = 16 / (int)sizeof(T);
+  constexpr int NP = 4 / VEC;            // packs per thread
+  constexpr int PR = BP / VEC;           // packs per column
+  constexpr int ZB = 8;                  // splits in flight
+  typedef XPack<T, VEC> pack_t;
+  __shared__ double zs[CW][BP + 1];
+  const int t = threadIdx.x, wv = t >> 6, lane = t & 63, g = lane >> 4, m = lane & 15;
+  const int64_t c0 = (int64_t)blockIdx.x * CW;
+  const int pt = wv % NPT, ct = wv / NPT;
+  // T operand of this wavefront's tile: K step st covers l = 4 st + g, masked
+  // to the triangle and to b (clamped, unconditional loads).
+  double bv[4 * NPT];
 #pragma unroll
-    for (int it = 0; it < NT; ++it) {
-      const int idx = threadIdx.x + 256 * it;
-      const int i = idx % BP, j = idx / BP;
-      tv[it] = a.Tm[i + (int64_t)(j < a.b ? j : 0) * a.ldt];
-    }
-#pragma unroll
-    for (int it = 0; it < NT; ++it) {
-      const int idx = threadIdx.x + 256 * it;
-      const int i = idx % BP, j = idx / BP;
-      Tl[i][j] = (i <= j && j < a.b) ? tv[it] : 0.0;
-    }
+  for (int st = 0; st < 4 * NPT; ++st) {
+    const int l = 4 * st + g, p = 16 * pt + m;
+    const int i = a.trans ? l : p, j = a.trans ? p : l;     // T[i][j], i <= j
+    bv[st] = a.Tm[i + (int64_t)min(j, a.b - 1) * a.ldt];
   }
-  const int p = threadIdx.x % BP, cl = threadIdx.x / BP;
-  // Rows [n, round_up(n, kUpdChunk)) of W are written as zeros so the update
-  // can stage whole chunks without predicates.
+  // Split sums: pack q = t + 256 u covers VEC values of column c0 + q / PR.
+  double z[NP][VEC];
+  const pack_t* zp[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int q = t + 256 * u;
+    const int64_t c = c0 + q / PR;
+    zp[u] = reinterpret_cast<const pack_t*>(a.Z + (c < a.n ? c : 0) * BP + VEC * (q % PR));
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) z[u][v] = 0.0;
+  }
+  const int64_t ss = a.split_stride / VEC;   // in packs (BP values per column)
+  for (int s0 = 0; s0 < a.nsplit; s0 += ZB) {
+    pack_t x[ZB][NP];
+#pragma unroll
+    for (int s = 0; s < ZB; ++s)
+#pragma unroll
+      for (int u = 0; u < NP; ++u) x[s][u] = zp[u][(int64_t)min(s0 + s, a.nsplit - 1) * ss];
+#pragma unroll
+    for (int s = 0; s < ZB; ++s)
+      if (s0 + s < a.nsplit)
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) z[u][v] += (double)x[s][u].v[v];
+  }
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    const int q = t + 256 * u;
+    const bool ok = c0 + q / PR < a.n;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) zs[q / PR][VEC * (q % PR) + v] = ok ? z[u][v] : 0.0;
+  }
+  __syncthreads();
+  d4_t acc = Mfma<double>::zero();
+#pragma unroll
+  for (int st = 0; st < 4 * NPT; ++st) {
+    const int l = 4 * st + g, p = 16 * pt + m;
+    const int i = a.trans ? l : p, j = a.trans ? p : l;
+    acc = Mfma<double>::op(zs[16 * ct + m][l], (i <= j && j < a.b) ? bv[st] : 0.0, acc);
+  }
+  // Rows [n, round_up(n, kUpdChunk)) of W are written as zeros (of their zero
+  // z) so the update can stage whole chunks without predicates.
   const int64_t n_pad = (a.n + kUpdChunk - 1) / kUpdChunk * kUpdChunk;
-  for (int64_t c0 = (int64_t)blockIdx.x * CPB; c0 < n_pad;
-       c0 += (int64_t)a.nfw * CPB) {
-    __syncthreads();
-    const int64_t c = c0 + cl;
-    // z_c = sum over the splits in split order, ZB loads in flight at a time
-    // (clamped split index, surplus loads not added).
-    const T* zp = a.Z + (c < a.n ? c : 0) * BP + p;
-    double z = 0.0;
-    for (int s0 = 0; s0 < a.nsplit; s0 += ZB) {
-      T v[ZB];
 #pragma unroll
-      for (int u = 0; u < ZB; ++u)
-        v[u] = zp[(int64_t)min(s0 + u, a.nsplit - 1) * a.split_stride];
-#pragma unroll
-      for (int u = 0; u < ZB; ++u)
-        if (s0 + u < a.nsplit) z += (double)v[u];
-    }
-    zs[cl][p] = c < a.n ? z : 0.0;
-    __syncthreads();
-    // Four independent partial sums (the terms past the triangle are zero in
-    // Tl), added in a fixed order.
-    double w4[4] = {0.0, 0.0, 0.0, 0.0};
-    if (a.trans) {
-      for (int l = 0; l <= p; l += 4)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (l + u < BP) w4[u] += Tl[l + u][p] * zs[cl][l + u];
-    } else {
-      for (int l = p & ~3; l < BP; l += 4)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) w4[u] += Tl[p][l + u] * zs[cl][l + u];
-    }
-    const double w = (w4[0] + w4[1]) + (w4[2] + w4[3]);
-    if (c < n_pad) a.W[c * BP + p] = (T)w;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t c = c0 + 16 * ct + Mfma<double>::drow(g, i);
+    if (c < n_pad) a.W[c * BP + 16 * pt + m] = (T)acc[i];
   }
 }
 
@@ -438,12 +455,12 @@ hipError_t launch_reduce(const ReduceArgs<T>& a, int nsplit, hipStream_t s) {
 template <typename T>
 hipError_t launch_formw(const FormWArgs<T>& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  const int cpb = 256 / a.bp;
-  int64_t blocks = ceil_div(a.n, cpb);
-  // Every workgroup stages all of T (bp^2 values): at 128 reflectors fewer
-  // workgroups, each over more columns, keep that re-read small.
-  const int64_t cap = a.bp == 128 ? 256 : 2048;
-  if (blocks > cap) blocks = cap;
+  // One workgroup per 1024 / bp columns (bp <= 64), rows of W padded to the
+  // update's chunk; the partials are 16-byte packs.
+  const int64_t blocks = ceil_div(round_up(a.n, kUpdChunk), std::max(1024 / a.bp, 1));
+  if (reinterpret_cast<uintptr_t>(a.Z) % 16 != 0 ||
+      a.split_stride * (int64_t)sizeof(T) % 16 != 0)
+    return hipErrorInvalidValue;
   // The gather's workgroups follow formW's.
   FormWArgs<T> a2 = a;
   a2.nfw = (int)blocks;
@@ -463,9 +480,7 @@ hipError_t launch_formw(const FormWArgs<T>& a, hipStream_t s) {
       if constexpr (std::is_same<T, double>::value) {
         if (!a.trans) {
           // The widest tile that still gives half the compute units a
-          // workgroup; the partials are 16-byte packs.
-          if (reinterpret_cast<uintptr_t>(a.Z) % 16 != 0 || a.split_stride % 2 != 0)
-            return hipErrorInvalidValue;
+          // workgroup.
           const int64_t n_pad = ceil_div(a.n, kUpdChunk) * kUpdChunk;
           if (ceil_div(n_pad, 16) >= 128)
             hipLaunchKernelGGL((formw128_kernel<16>), dim3((unsigned)ceil_div(n_pad, 16)),
@@ -478,10 +493,8 @@ hipError_t launch_formw(const FormWArgs<T>& a, hipStream_t s) {
                                dim3(256), 0, s, a);
           break;
         }
-        hipLaunchKernelGGL((formw_kernel<T, 128>), grid, dim3(256), 0, s, a2);
-        break;
       }
-      return hipErrorInvalidValue;
+      return hipErrorInvalidValue;   // (no caller: 128 reflectors, transposed)
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
