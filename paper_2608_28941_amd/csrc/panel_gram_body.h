@@ -114,6 +114,8 @@ struct GramLds {
   double red2[256];
   double fx;                      // norm^2 below the diagonal, sweep's first column
   int js, stopped;                // of the block just factored
+  int je;                         // end of its rows of R and W: js, or the sweep's
+                                  // first column where that is left as it is
 };
 
 // One 16 x 16 block of a sweep: lane (h, k) holds rows 4 h + i of column k.
@@ -491,10 +493,12 @@ __device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelA
         const int nb = min(16, b - 16 * J);
         s.js = nb;
         s.unchecked = first ? o : -1;
+        const bool none = first && !(L.fx > 0.0);
         s.todo = ((1u << nb) - 1u) & ~((1u << o) - 1u);
-        if (first && !(L.fx > 0.0)) {
+        if (none) {
           // Nothing below the diagonal in the sweep's first column: H = I,
-          // V's column zero, tau = 0, and the sweep ends after it.
+          // V's column zero, tau = 0, and the sweep ends after it.  No step
+          // runs, so the inverses have no rows: R and W have none either.
           s.js = o + 1;
           s.todo = 0;
           if (m16 == o) s.rwl = 0.0;
@@ -513,14 +517,15 @@ __device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelA
         if (t >= o && t < s.js) L.tau[16 * J + t] = s.tau;
         if (t == 0) {
           L.js = s.js;
+          L.je = none ? o : s.js;
           L.stopped = (whole && s.todo != 0) ? 0 : 1;
         }
       }
       __syncthreads();
-      const int js = L.js;
+      const int js = L.js, je = L.je;
       const bool stopped = L.stopped != 0;
       first = false;
-      // R_JK over F_JK (rows [o, js), the others zero) and V in the top rows
+      // R_JK over F_JK (rows [o, je), the others zero) and V in the top rows
       // below the block.
       {
         const int t = opaque(t0), lane = t & 63, g = lane >> 4, m16 = lane & 15;
@@ -533,7 +538,7 @@ __device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelA
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int r = g + 4 * i;
-              Fk[r * kTs + m16] = (r >= o && r < js) ? d[i] : 0.0;
+              Fk[r * kTs + m16] = (r >= o && r < je) ? d[i] : 0.0;
             }
           } else {
             double* X = L.top + 16 * (J + 1 + u - nk) * LT + 16 * J;
@@ -543,7 +548,7 @@ __device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelA
           }
         }
         if (nk > 0) __syncthreads();
-        // W_JK = V_JJ^-1 (X_JK - R_JK), rows [o, js).
+        // W_JK = V_JJ^-1 (X_JK - R_JK), rows [o, je).
         for (int u = wv; u < nk; u += 4) {
           const int K = J + 1 + u;
           const double* Fk = L.k.F[Geo::tile(J, K)];
@@ -557,7 +562,7 @@ __device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelA
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int r = g + 4 * i;
-            L.k.W[r * LT + 16 * K + m16] = (r >= o && r < js) ? d[i] : 0.0;
+            L.k.W[r * LT + 16 * K + m16] = (r >= o && r < je) ? d[i] : 0.0;
           }
         }
         if (nk > 0) __syncthreads();
@@ -581,7 +586,7 @@ __device__ __forceinline__ void panel_gram_body(GramLds<BP>& L, const GramPanelA
             for (int s4 = 0; s4 < 4; ++s4) {
               const int kk = 4 * s4 + g;
               const double v = topJ[m16 * LT + 16 * J + kk];
-              d = Mfma<double>::op((kk >= o && kk < js) ? v : 0.0, L.k.W[kk * LT + 16 * K + m16], d);
+              d = Mfma<double>::op((kk >= o && kk < je) ? v : 0.0, L.k.W[kk * LT + 16 * K + m16], d);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

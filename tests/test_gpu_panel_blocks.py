@@ -52,3 +52,29 @@ def test_panel_sweep_ends_inside_a_block(m, b, drop):
     Y = W.random_dense(m, b, np.float64, 7 + drop)
     Y[:, drop:] = Y[:, :1] + 1e-3 * Y[:, drop:]
     _check(np.asfortranarray(Y), 100 * 1e4 * 2.3e-16)
+
+
+@pytest.mark.parametrize("m,b,zero", [(3000, 64, [11]), (3000, 48, [12, 13]), (9000, 64, [0, 14]),
+                                      (200, 64, [15, 16, 63]), (5000, 32, [0, 11, 31]),
+                                      (5000, 16, [3, 15])])
+def test_panel_columns_zero_below_the_diagonal(m, b, zero):
+    # H = I for them, in whatever place of a 16-column block they stand.
+    say(f"panel zero columns m={m} b={b} zero={zero}")
+    Y = W.random_graded(m, b, np.float64, 31 + m + b, decay=1e-2)
+    Y[:, zero] = 0.0
+    _check(Y, 1e4 * 2.3e-16)
+
+
+@pytest.mark.parametrize("rows", [12, 16])
+def test_run_on_a_matrix_of_few_nonzero_rows(rows):
+    # The first panel's columns from `rows` on are zero below the diagonal.
+    say(f"run few rows {rows}")
+    A = np.zeros((700, 400), order="F")
+    A[:rows] = W.random_dense(rows, 400, np.float64, rows)
+    ref = oracle.hbarrf(A, 1e-8, 48, 5)
+    with rrf.Plan(torch.float64, 700, 400, 48) as p:
+        Q, B, k = p.run(to_dev(A), 1e-8, 48, 5)
+        Q, B = to_host(Q), to_host(B)
+    assert k == ref.k
+    assert np.linalg.norm(Q.T @ Q - np.eye(k)) < 1e-12
+    assert np.linalg.norm(A - Q @ B) < 1e-13 * np.linalg.norm(A)
