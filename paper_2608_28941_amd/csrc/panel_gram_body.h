@@ -158,7 +158,8 @@ __device__ __forceinline__ void gram_block_step(GramBlock& s, double* inv, const
   const double rb = (alpha >= 0.0) ? -y : y;        // 1 / beta
   const double wjj = fma(-nrm2, rb, alpha);         // alpha - beta
   const double rw = fast_rcp(wjj);
-  const double fc = fk * (y * y);
+  // (y^2 would overflow for column norms below 7.5e-155.)
+  const double fc = (fk * y) * y;
 #pragma unroll
   for (int i = 0; i < 4; ++i) s.f[i] = fma(-fr[i], fc, s.f[i]);
   const double wk = (k > J) ? fma(-fk, rb, xk) : 0.0;   // W_Jk = X_Jk - R_Jk
@@ -175,9 +176,9 @@ __device__ __forceinline__ void gram_block_step(GramBlock& s, double* inv, const
     const double a0 = row_of<QJ>(s.aux[IJ]);
     const double ak = r1 ? a0 * rb : a0;
     if (h == QJ) inv[J * kTs + k] = ak;
-    const double ac = ak * (r1 ? rb : rw);
+    const double rs = r1 ? rb : rw;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s.aux[i] = fma(-(r1 ? fr[i] : xr[i]), ac, s.aux[i]);
+    for (int i = 0; i < 4; ++i) s.aux[i] = fma(-((r1 ? fr[i] : xr[i]) * rs), ak, s.aux[i]);
   }
 }
 

@@ -2,8 +2,8 @@
 // workgroups of it and writes V, T and tau.  LDS starts as the byte given, so
 // that a value read before it is written shows.
 //   host_panel_gram BP RT G b m fill in.bin out.bin
-// in: m x b doubles, column-major; out: V (m x b), T (b x b), tau (b), then
-// the wait error.
+// in: m x b doubles, column-major; out: V (m x b), T (b x b), tau (b), the
+// number of grid exchanges (G > 1) and the wait error.
 
 #include "host_wavefront.h"
 
@@ -42,7 +42,11 @@ static int go(int G, int b, int64_t m, int fill, const char* in, const char* out
   for (int c = 0; c < b; ++c) std::fwrite(&V[c * ld], 8, (size_t)m, f);
   for (int c = 0; c < b; ++c) std::fwrite(&T[c * 64], 8, (size_t)b, f);
   std::fwrite(tau.data(), 8, (size_t)b, f);
-  const double err = st.barrier_err;
+  // The exchanges are numbered by their words' epochs.
+  unsigned last = a.p.epoch_base;
+  for (unsigned long long x : sums) last = std::max(last, (unsigned)x);
+  const double exchanges = last - a.p.epoch_base, err = st.barrier_err;
+  std::fwrite(&exchanges, 8, 1, f);
   std::fwrite(&err, 8, 1, f);
   std::fclose(f);
   return 0;

@@ -20,7 +20,8 @@ U = np.finfo(np.float64).eps / 2
 
 @pytest.fixture(scope="module")
 def panel(tmp_path_factory):
-    """panel(Y, G, rt) -> V, T, tau of the compiled body."""
+    """panel(Y, G, rt) -> V, T, tau of the compiled body; panel.exchanges: the
+    grid exchanges of the last call (G > 1)."""
     clang = next((c for c in (os.path.join(ROCM, "llvm", "bin", "clang++"),
                               shutil.which("amdclang++")) if c and os.path.exists(c)), None)
     if clang is None:
@@ -52,6 +53,7 @@ def panel(tmp_path_factory):
         assert r.returncode == 0
         o = np.fromfile(fout)
         assert o[-1] == 0          # no wait gave up
+        go.exchanges = int(o[-2])
         return (o[:m * b].reshape(b, m).T, o[m * b:m * b + b * b].reshape(b, b).T,
                 o[m * b + b * b:m * b + b * b + b])
 
@@ -97,3 +99,25 @@ def test_panel_of_few_nonzero_rows(panel, rows):
     V, T, tau = panel(Y, 2)
     _check(Y, V, T, tau)
     assert np.all(tau[rows:] == 0)
+
+
+@pytest.mark.parametrize("cols", [slice(None), slice(20, None), slice(None, None, 2)])
+@pytest.mark.parametrize("e", [-515, -520, -525])
+def test_tiny_columns(panel, e, cols):
+    # Norms whose squares are subnormal: the reciprocal of the square overflows,
+    # which must neither reach a result nor end the sweep at every column.
+    Y = np.random.default_rng(40).standard_normal((100, 40))
+    tau_o = oracle.geqr2(Y)[1]
+    S = Y.copy()
+    S[:, cols] = np.ldexp(S[:, cols], e)
+    panel(Y, 2)
+    sweeps = panel.exchanges
+    V, T, tau = panel(S, 2)
+    assert panel.exchanges <= sweeps + 1
+    assert np.all(np.isfinite(V)) and np.all(np.isfinite(T))
+    # A scale changes no tau.  A square of about 2^(2 e) is rounded to 2^-1074:
+    # the norms' relative errors are about 2^(-1074 - 2 e), and 1e3 covers their
+    # growth over 40 columns (as 1e4 above does for u).
+    tol = 1e3 * 2.0 ** (-1074 - 2 * e) + 1e4 * U
+    assert np.max(np.abs(tau - tau_o)) < tol
+    assert np.linalg.norm(T.T @ (V.T @ V) @ T - T - T.T) < 10 * tol
