@@ -567,11 +567,37 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
           ? 1 : std::max<int64_t>(1, std::min<int64_t>(kMaxSuper, super_cols / b));
   for (PanelShape shs; per_sub > 1; --per_sub)
     if (gram_panel_shape(m, (int)std::min(per_sub * b, kcap), p->num_cus, &shs)) break;
-  const int64_t bs = per_sub * b;     // columns between host-side stop tests
+  // A run that stops early would pay for columns that it drops (4096 x 4096
+  // fp32, b = 16, one block: 0.47 ms at 64 columns, 0.31 at 16; 131072 x 2048
+  // fp64, b = 32: 3.2 and 2.1), so a sub-block takes 32 columns until the stop
+  // is known to be far: the last two states read (after k0 and k1 columns, the
+  // stopping quantity E0 and E1), extrapolated geometrically, leave more than
+  // that from here on.  With look-ahead the change of width costs a panel that
+  // no update hides (about 0.1 ms): only after six sub-blocks, with four of
+  // the wide ones to come, and then for good.
+  const int64_t narrow = std::min(per_sub, std::max<int64_t>(1, 32 / b));
+  bool la = false;           // look-ahead (below)
+  int64_t k0 = 0, k1 = 0;
+  double E0 = 0.0, E1 = 0.0;
+  std::vector<std::pair<int64_t, int64_t>> subs;   // start, width, as first asked for
   auto sub_width = [&](int64_t kk) -> int64_t {
     if (kk >= kcap) return 0;
-    const int64_t be = std::min((kk / bs) * bs + bs, kcap);
-    return std::min<int64_t>(sub_max, be - kk);
+    for (size_t i = subs.size(); i-- > 0;)
+      if (subs[i].first == kk) return subs[i].second;
+    int64_t nb = per_sub;
+    const bool wide = !subs.empty() && subs.back().second > narrow * b;
+    if (per_sub > narrow && tol > 0.0 && !(la && wide)) {
+      double left = 0.0;     // blocks from kk to the stop
+      if (k1 >= (la ? 6 * narrow * b : b)) {
+        const double rate = std::log(E0 / E1) / (double)(k1 - k0);
+        const double at = (double)k1 + std::log(E1 / p->st_host->sigma2) / rate;
+        left = rate > 0.0 ? (at - (double)kk) / (double)b : (double)kcap;
+      }
+      if (!(left > (double)(la ? 4 * per_sub : narrow))) nb = narrow;
+    }
+    const int64_t be = std::min((kk / b) * b + nb * b, kcap);
+    subs.emplace_back(kk, std::min<int64_t>(sub_max, be - kk));
+    return subs.back().second;
   };
   // Work credited to a stage for the sub-block that starts at column col,
   // taken back after the run if the run stopped before that sub-block (a
@@ -634,6 +660,12 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   if (he != hipSuccess) return hip_fail(he);
   if (p->st_host->barrier_err) return RRF_ERR_INTERNAL;
   if (p->st_host->nonfinite) return RRF_ERR_NONFINITE;
+  // The quantity that the stop test compares, as last read.
+  auto stop_quantity = [&]() -> double {
+    return mode == RRF_STOP_TRAILING ? p->st_host->E_trail
+           : (mode == RRF_STOP_SUBTRACT ? p->st_host->E_sub : p->st_host->E_spec);
+  };
+  E1 = p->st_host->E0;       // after no column
   const int power = p->power;
   if (power > 0)
     RRF_LAUNCH(p, RRF_STAGE_SAMPLE, 0.0, 0.0, launch_scaled_identity(p->Tpow, 64, p->st, s));
@@ -658,21 +690,21 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   // launch of its own.
   const int alg0 = panel_alg(p);
   const bool la_gram = alg0 == kPanelGram;
-  bool la = p->lookahead != 0 && power == 0 && kcap > b0 && (alg0 == kPanelGrid || la_gram) &&
+  la = p->lookahead != 0 && power == 0 && kcap > b0 && (alg0 == kPanelGrid || la_gram) &&
             (double)m * (double)n * e <= kLookaheadBytes;
   // Blocks of more than 64 columns whose last sub-block is narrower (96: 64 and
   // 32): the panel of one width does not run inside the update of the other,
   // and the look-ahead without that only adds the redundant panel update
   // (8169 x 461 fp32, b = 96: 1.41 ms with it, 1.18 without).
-  if (bs > sub_max && bs % sub_max != 0 && pad16(bs % sub_max) != pad16(sub_max)) la = false;
+  if (b > sub_max && b % sub_max != 0 && pad16(b % sub_max) != pad16(sub_max)) la = false;
   // The shape of the look-ahead panel of a sub-block (mr rows, width bb).
   auto la_shape = [&](int64_t mr, int64_t bb, PanelShape* sh) -> bool {
     if (la_gram) return gram_fused_shape(mr, (int)bb, p->gram_fused_max, sh);
     return panel_shape(mr, (int)bb, p->num_cus, p->panel_target, sh) && sh->G <= p->num_cus / 4;
   };
   if (la) {
-    PanelShape sh1;
-    la = la_shape(m - b0, sub_width(b0), &sh1);
+    PanelShape sh1;          // of the widest panel to come
+    la = la_shape(m - b0, std::min({per_sub * b, (int64_t)sub_max, kcap - b0}), &sh1);
   }
   int64_t k = 0;
   int64_t yoff = 0;          // row offset of the next sample in the slabs
@@ -682,7 +714,6 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   bool stop = p->st_host->stop != 0;
   bool w_ready = false;      // W of this sub-block was formed at the end of the last one
   bool w_gathered = false;   // ... together with its look-ahead gather
-  double E_prev2 = 0.0;      // the stopping quantity one state read earlier
   int64_t trim_from = 0, trim_to = 0;   // columns of the last sub-block past the final k
   // Stages credited with the panel of this sub-block and the next one.
   int last_panel_stage = RRF_STAGE_PANEL, next_panel_stage = RRF_STAGE_PANEL;
@@ -822,7 +853,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     const int64_t mp = m - k;
     p->sub_start.push_back(k);
     const int64_t k_next = k + bi;
-    const bool at_end = k_next == kcap || k_next % bs == 0;  // a stop test follows
+    const bool at_end = k_next == kcap || k_next % b == 0;   // a stop test follows
     const int64_t b_next = sub_width(k_next);
     bool s1_done = false;      // sub-block 0: S_1 = A Omega_1 taken with the panel
     last_panel_stage = next_panel_stage;
@@ -1062,15 +1093,13 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     // without look-ahead the next block's gather and panel (they need only
     // the sample this update took), with look-ahead (the next panel is
     // already factored) its reduce and formW.  It is queued when the
-    // stopping quantity, extrapolated geometrically from the last two state
-    // reads, stays above sigma^2 after this block; a wrong guess (the run
+    // stopping quantity, extrapolated geometrically from the last two states
+    // read, stays above sigma^2 after this block; a wrong guess (the run
     // stops here after all) wastes that work, whose results lie past k and
     // are never used.
-    const double E_prev = mode == RRF_STOP_TRAILING ? p->st_host->E_trail
-                          : (mode == RRF_STOP_SUBTRACT ? p->st_host->E_sub : p->st_host->E_spec);
     const double E_pred =
-        E_prev2 > 0.0 ? E_prev * std::min(1.0, E_prev / E_prev2) : E_prev;
-    E_prev2 = E_prev;
+        k1 > 0 ? E1 * std::min(1.0, std::pow(E1 / E0, (double)(k_next - k1) / (double)(k1 - k0)))
+               : E1;
     const bool more_likely = b_next > 0 && E_pred > p->st_host->sigma2;
     bool next_panel = false, next_w = false;
     PanelShape shn{};
@@ -1138,6 +1167,10 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     if (next_w) w_ready = true;
     if (p->st_host->barrier_err) return RRF_ERR_INTERNAL;
     if (p->st_host->nonfinite) return RRF_ERR_NONFINITE;
+    k0 = k1;
+    E0 = E1;
+    k1 = k;
+    E1 = stop_quantity();
   }
   p->nblocks = blk;
   p->t_blocks = per_sub > 1 ? b : 0;

@@ -65,3 +65,49 @@ def test_rank_cap_inside_a_sub_block(b, kmax):
         assert p.trace()["nblocks"] == -(-kmax // b)
         # cond(A Omega_k) is about 10^(kmax / 30): well inside 1e-9.
         assert np.max(np.abs(to_host(Q) - ref.Q)) < 1e-9
+
+
+@pytest.mark.parametrize("m,n,b", [(1100, 900, 16), (1100, 900, 24), (1500, 1400, 8)])
+def test_early_stop_takes_at_most_32_columns(m, n, b):
+    # A run that its first block ends: the first sample (the only one that is
+    # not taken back as queued ahead; the panel beside the second one adds
+    # 3 m 32^2 at most) holds at most 32 columns.
+    say(f"early stop m={m} n={n} b={b}")
+    A = W.random_dense(m, b - 3, np.float64, b) @ W.random_dense(b - 3, n, np.float64, b + 1)
+    with rrf.Plan(torch.float64, m, n, b) as p:
+        Q, B, k = p.run(to_dev(np.asfortranarray(A)), 1e-8, b, 3)
+        sample = p.stage_stats()["sample"]["flops"]
+        Q, B = to_host(Q), to_host(B)
+    assert k == b
+    assert sample <= 2.0 * m * n * 32 + 3.0 * m * 32 ** 2
+    assert np.linalg.norm(A - Q @ B) < 1e-12 * np.linalg.norm(A)
+
+
+@pytest.mark.parametrize("lookahead", ["1", "0"])
+@pytest.mark.parametrize("b", [8, 16, 24, 32])
+def test_sub_blocks_widen_on_the_way(monkeypatch, b, lookahead):
+    # A slow decay: 32 columns at first, 64 once the stop is known to be far.
+    monkeypatch.setenv("RRF_LOOKAHEAD", lookahead)
+    say(f"sub-blocks widen b={b} lookahead={lookahead}")
+    m, n, tol = 1100, 900, 3e-3
+    A = W.random_graded(m, n, np.float64, 17)
+    ref = oracle.hbarrf(A, tol, b, 9)
+    with rrf.Plan(torch.float64, m, n, b) as p:
+        Q, B, k = p.run(to_dev(A), tol, b, 9)
+        tr, updates = p.trace(), p.stage_stats()["update"]["launches"]
+        V, T, _ = p.reflectors(m, k)
+        Q, B, V, T = to_host(Q), to_host(B), to_host(V), to_host(T)
+    assert k == ref.k and tr["nblocks"] == len(ref.trace)
+    # At most one pass per min(4 blocks, 64 columns), and the first 32-column
+    # ones: 8 with look-ahead, 2 without.
+    cols = min(4, 64 // b) * b
+    assert updates <= 1 + -(-k // cols) + (8 if lookahead == "1" else 2)
+    assert np.allclose(tr["E_trail"], [t[1] for t in ref.trace], rtol=1e-9, atol=0)
+    # cond(A Omega_k) is at most about 1e4 here.
+    assert np.max(np.abs(Q - ref.Q)) < 1e3 * 1e4 * 2.3e-16
+    assert np.linalg.norm(B - Q.T @ A) < 1e-12 * np.linalg.norm(A)
+    for i in range(0, k, b):
+        c = slice(i, min(i + b, k))
+        w = c.stop - c.start
+        Vi, Ti = V[:, c], np.triu(T[:w, c])
+        assert np.linalg.norm(Ti.T @ (Vi.T @ Vi) @ Ti - Ti - Ti.T) < 1e-11
