@@ -387,13 +387,12 @@ int panel_alg(const rrf_plan* p) {
   return p->panel_mode != kPanelAuto ? p->panel_mode : kPanelGram;
 }
 
-// The route an m x b panel takes: the plan's algorithm when its
+// The route an m x b panel takes: algorithm alg when its
 // register-resident grid fits on the device, else the tall-skinny QR, whose
 // tree has no register-capacity bound (Alg. 2 puts no limit on m).  -1 if
 // no route fits (beyond the tree's depth).  sh->rows_pad is the row count
 // the gathered panel must cover.
-int panel_route(const rrf_plan* p, int64_t m, int b, PanelShape* sh) {
-  const int alg = panel_alg(p);
+int panel_route(const rrf_plan* p, int64_t m, int b, PanelShape* sh, int alg) {
   if (alg == kPanelGram && gram_panel_shape(m, b, p->num_cus, sh)) return kPanelGram;
   if (alg == kPanelGrid && panel_shape(m, b, p->num_cus, p->panel_target, sh)) return kPanelGrid;
   TsqrShape ts;
@@ -403,6 +402,9 @@ int panel_route(const rrf_plan* p, int64_t m, int b, PanelShape* sh) {
   sh->G = 0;
   sh->rows_pad = ts.rows_pad;
   return kPanelTsqr;
+}
+int panel_route(const rrf_plan* p, int64_t m, int b, PanelShape* sh) {
+  return panel_route(p, m, b, sh, panel_alg(p));
 }
 bool panel_fits(const rrf_plan* p, int64_t m, int b, PanelShape* sh) {
   return panel_route(p, m, b, sh) >= 0;
@@ -1382,8 +1384,15 @@ template <typename T>
 rrf_status panel_stage(rrf_plan* p, const T* Y, int64_t m, int64_t b,
                        int64_t ldy, T* Vout, int64_t ldv, T* Tout, int64_t ldt,
                        T* tauout) {
+  // A binary64 panel of more than 32 columns on its own takes its norms column
+  // by column: the downdated Gram matrix leaves two to three times the error
+  // in V (8192 x 64, condition 100: 8.9e-14 against 3.2e-14; 179 and 341 us),
+  // and sweeps short enough for the same error cost as many exchanges.  A
+  // run's Q and B, and results rounded to binary32, do not show it.
+  const int alg = p->panel_mode == kPanelAuto && std::is_same<T, double>::value && b > 32
+                      ? kPanelGrid : panel_alg(p);
   PanelShape sh;
-  const int route = panel_route(p, m, (int)b, &sh);
+  const int route = panel_route(p, m, (int)b, &sh, alg);
   if (route < 0) return RRF_ERR_SHAPE;
   hipStream_t s = p->stream;
   hipError_t e = clear_wait_error(p);

@@ -17,7 +17,10 @@ pytestmark = pytest.mark.gpu
 
 def _check(Y, tol):
     m, b = Y.shape
-    with rrf.Plan(torch.float64, m, b, b) as p:
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setenv("RRF_PANEL", "gram")     # (a panel of > 32 columns on its own: the grid)
+        p = rrf.Plan(torch.float64, m, b, b)
+    with p:
         V, T, tau = (to_host(x) for x in p.panel_qr(to_dev(Y)))
     V_o, tau_o = oracle.geqr2(Y)
     # Householder QR is backward stable: the reflectors agree to cond(Y) u

@@ -69,6 +69,39 @@ def test_panel_qr_matches_oracle(monkeypatch, mode, dtype, m, b, seed):
     assert np.all(np.triu(V, 1) == 0) and np.all(np.diag(V) == 1)
 
 
+def _geqr2_extended(Y):
+    """V of Householder QR with the sums in extended precision."""
+    A = Y.astype(np.longdouble)
+    V = np.zeros_like(A)
+    for j in range(A.shape[1]):
+        x = A[j:, j].copy()
+        beta = -np.copysign(np.sqrt(np.sum(x * x)), x[0])
+        tau, v = (beta - x[0]) / beta, x / (x[0] - beta)
+        v[0] = 1
+        V[j:, j] = v
+        A[j:, j + 1:] -= tau * np.outer(v, v @ A[j:, j + 1:])
+    return V
+
+
+@pytest.mark.parametrize("m,b,decay", [(1000, 64, 1e-2), (1000, 40, 1.0), (1000, 48, 1e-4)])
+def test_wide_panel_has_the_errors_of_direct_sums(m, b, decay):
+    # A binary64 panel of more than 32 columns on its own: V as close to the
+    # exact one as column-by-column binary64 sums give it (the oracle's; the
+    # downdated Gram matrix leaves two to three times that).
+    say(f"panel errors m={m} b={b} decay={decay}")
+    ratio = []
+    with rrf.Plan(torch.float64, m, b, b) as p:
+        for seed in range(6):
+            g = np.random.default_rng(60 + seed)
+            mix = g.standard_normal((b, b)) * np.logspace(0.0, np.log10(decay), b)
+            Y = np.asfortranarray(g.standard_normal((m, b)) @ mix.T)
+            X = _geqr2_extended(Y)
+            V = to_host(p.panel_qr(to_dev(Y))[0])
+            ratio.append(float(np.linalg.norm((V - X).astype(float)) /
+                               np.linalg.norm((oracle.geqr2(Y)[0] - X).astype(float))))
+    assert np.exp(np.mean(np.log(ratio))) < 1.6, ratio
+
+
 def _rank_deficient(m, b, r, seed):
     g = np.random.default_rng(seed)
     return np.asfortranarray(g.standard_normal((m, r)) @ g.standard_normal((r, b)))
