@@ -44,7 +44,7 @@ constexpr int kOmLd = 256;        // Omega stored [c][q]: a batch of 256 sketch 
 constexpr int kPanelGrid = 0;      // column-by-column panel, one grid reduction per column
 constexpr int kPanelTsqr = 1;      // tall-skinny QR + Householder reconstruction
 constexpr int kPanelGram = 2;      // column recurrence from the Gram matrix, one exchange per sweep
-constexpr int kPanelAuto = 3;      // kPanelGram
+constexpr int kPanelAuto = 3;      // kPanelGram; for wide binary64 panels on their own kPanelGrid
 constexpr int kTLd = 64;          // T stored like geqrt's T: 64 rows
 constexpr size_t kStateBytes = 256;                     // pinned: state, then traces
 static_assert(sizeof(DevState) <= kStateBytes, "the traces follow the state");
@@ -381,8 +381,8 @@ hipError_t read_state(rrf_plan* p) {
   return hipStreamSynchronize(p->stream);
 }
 
-// The panel algorithm: the Gram form (one grid exchange per sweep of columns)
-// unless the plan forces another.
+// The panel algorithm of a run: the Gram form (one grid exchange per sweep of
+// columns) unless the plan forces another.
 int panel_alg(const rrf_plan* p) {
   return p->panel_mode != kPanelAuto ? p->panel_mode : kPanelGram;
 }
@@ -688,12 +688,9 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   // panel update take cost more than the panel on its own: 31.5 ms per run
   // with the look-ahead, 30.8 without; at 4096 x 11008 fp32 (172 MiB) 8.5 with
   // it, 9.3 without, at 4096 x 4096 fp32 10.4 and 12.4.
-  // A forced column-by-column panel (RRF_PANEL=grid) follows the update in a
-  // launch of its own.
-  const int alg0 = panel_alg(p);
-  const bool la_gram = alg0 == kPanelGram;
-  la = p->lookahead != 0 && power == 0 && kcap > b0 && (alg0 == kPanelGrid || la_gram) &&
-            (double)m * (double)n * e <= kLookaheadBytes;
+  // Gram panels only (a forced panel of another kind has no such launch).
+  la = p->lookahead != 0 && power == 0 && kcap > b0 && panel_alg(p) == kPanelGram &&
+       (double)m * (double)n * e <= kLookaheadBytes;
   // Blocks of more than 64 columns whose last sub-block is narrower (96: 64 and
   // 32): the panel of one width does not run inside the update of the other,
   // and the look-ahead without that only adds the redundant panel update
@@ -701,8 +698,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
   if (b > sub_max && b % sub_max != 0 && pad16(b % sub_max) != pad16(sub_max)) la = false;
   // The shape of the look-ahead panel of a sub-block (mr rows, width bb).
   auto la_shape = [&](int64_t mr, int64_t bb, PanelShape* sh) -> bool {
-    if (la_gram) return gram_fused_shape(mr, (int)bb, p->gram_fused_max, sh);
-    return panel_shape(mr, (int)bb, p->num_cus, p->panel_target, sh) && sh->G <= p->num_cus / 4;
+    return gram_fused_shape(mr, (int)bb, p->gram_fused_max, sh);
   };
   if (la) {
     PanelShape sh1;          // of the widest panel to come
@@ -870,7 +866,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
       // Sub-block 0 with look-ahead: its panel beside the first look-ahead
       // sample, in the shape of a panel inside an update's launch.
       int occ0 = 0;
-      if (la && la_gram && sub == 0 && b_next > 0 && pad16(b_next) == bp &&
+      if (la && sub == 0 && b_next > 0 && pad16(b_next) == bp &&
           la_shape(mp, bi, &shf) && update_gram_supported(0, bp, shf))
         occ0 = update_gram_occupancy<T>(shf, true);
       const bool with_sample = occ0 > 0 && (int64_t)occ0 * p->num_cus > shf.G;
@@ -1012,7 +1008,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
     ua.W = (T*)p->W; ua.ldw = bp; ua.Om = om_win; ua.ldo = kOmLd; ua.qp = q_s;
     ua.P = Yp; ua.ldp = ldb; ua.split_stride = ldb * 64; ua.s0 = bi;
     ua.normpart = p->normpart;
-    const bool fused = panel_ready && la_gram && update_gram_supported(bp, q_s, pan_shape);
+    const bool fused = panel_ready && update_gram_supported(bp, q_s, pan_shape);
     int su0 = upd_splits(mp, n, p->num_cus, usmax);
     if (fused) {
       const int occ = update_gram_occupancy<T>(pan_shape, false);
@@ -1051,7 +1047,7 @@ rrf_status run_impl(rrf_plan* p, const T* A, int64_t m, int64_t n, int64_t lda,
         RRF_LAUNCH(p, RRF_STAGE_UPDATE, upd_flops, 2.0 * e * mp * n,
                    launch_update<T>(ua, su, s));
         RRF_LAUNCH(p, RRF_STAGE_PANEL, pan_flops, pan_bytes,
-                   run_panel(p, pan, la_gram ? kPanelGram : kPanelGrid, pan_shape, s));
+                   run_panel(p, pan, kPanelGram, pan_shape, s));
         spec(RRF_STAGE_PANEL, k_next, pan_flops, pan_bytes);
       }
     } else {
@@ -1525,8 +1521,9 @@ rrf_status plan_create(rrf_plan_t* plan, int dtype_bits, int64_t m_max, int64_t 
   p->lookahead = 1;
   if (const char* la = std::getenv("RRF_LOOKAHEAD")) p->lookahead = std::atoi(la) != 0;
   // RRF_PANEL selects the panel algorithm: "grid" (column by column, one
-  // grid-wide reduction per column), "gram" (the default: the same reflectors
-  // from the Gram matrix, one grid exchange per sweep of columns), "tsqr"
+  // grid-wide reduction per column), "gram" (the same reflectors from the Gram
+  // matrix, one grid exchange per sweep of columns; the default but for wide
+  // binary64 panels of rrf_panel_qr), "tsqr"
   // (tall-skinny QR with Householder reconstruction).  The look-ahead
   // factors gram panels inside the update's launch.
   p->panel_mode = kPanelAuto;

@@ -150,6 +150,23 @@ def test_scaled_workloads_gram_panel(monkeypatch, name, m, n, b, tol):
     _check_against_live_oracle(w, W.build_matrix(w))
 
 
+@pytest.mark.parametrize("name,m,n,b,tol", [SCALED[1], SCALED[2], SCALED[3], SCALED[5]])
+def test_scaled_workloads_grid_panel(monkeypatch, name, m, n, b, tol):
+    # Same bar with the column-by-column panel.  No update's launch holds it,
+    # so it runs without look-ahead: the launches are those of RRF_LOOKAHEAD=0.
+    monkeypatch.setenv("RRF_PANEL", "grid")
+    w = W.scaled(name, m, n, block_b=b, tol=tol)
+    A = W.build_matrix(w)
+    _check_against_live_oracle(w, A)
+    launches = []
+    for la in ("1", "0"):
+        monkeypatch.setenv("RRF_LOOKAHEAD", la)
+        with rrf.Plan(_tdt(w.dtype), m, n, w.block_b) as p:
+            p.run(to_dev(A), w.tol, w.block_b, w.sketch_seed)
+            launches.append([v["launches"] for v in p.stage_stats().values()])
+    assert launches[0] == launches[1]
+
+
 @pytest.mark.parametrize("name", W.GAP_INPUTS)
 def test_gap_inputs_gram_panel(monkeypatch, name):
     monkeypatch.setenv("RRF_PANEL", "gram")
