@@ -108,6 +108,8 @@ typedef enum rrf_stage {
  *                as sub-blocks of at most 64 columns (the last one ragged):
  *                Householder QR is column by column, so the reflectors are
  *                the block's own; the stop test runs once per block.
+ *                Several blocks of at most 32 columns share a sub-block where
+ *                the run is expected to go on.
  *   k_max        rank cap (>= 0); 0 means min(m, n).  A cap below the rank the
  *                tolerance needs is the fixed-rank mode of Sec. 6 (Fig. 6).
  *   hip_stream   hipStream_t to enqueue on; NULL means the null stream.
@@ -249,8 +251,11 @@ rrf_status rrf_sketch(rrf_dtype dtype, uint64_t seed, int64_t n, int64_t col0,
  * Outputs: V (m x b, ldv >= m, unit lower trapezoidal with explicit ones and
  * zeros), T (b x b upper triangular, ldt >= b, lower part zeroed), tau (b).
  * Requires 1 <= b <= min(plan's block_b_max, 64), b <= m <= plan's m_max.
- * Panels taller than the register-resident grid holds take the tall-skinny
- * QR tree (RRF_ERR_SHAPE only beyond it).  Synchronises the plan's stream;
+ * An RRF_F64 panel of more than 32 columns is factored column by column (V
+ * as accurate as direct sums give it; up to 65536 rows on 256 CUs), others from
+ * their Gram matrix as in rrf_run; RRF_PANEL chooses for all.  Panels taller
+ * than the register-resident grid holds take the tall-skinny QR tree
+ * (RRF_ERR_SHAPE only beyond it).  Synchronises the plan's stream;
  * RRF_ERR_INTERNAL if a grid-wide wait gave up (outputs undefined). */
 rrf_status rrf_panel_qr(rrf_plan_t plan, const void* Y, int64_t m, int64_t b,
                         int64_t ldy, void* V, int64_t ldv, void* T,

@@ -1901,7 +1901,8 @@ rrf_status rrf_subspace_map(rrf_plan_t plan, const void* Qnew, int64_t ldqn,
     hipError_t he = hipMemset2DAsync(out, (size_t)ldo * e, 0, (size_t)r_new * e, (size_t)n, s);
     return he == hipSuccess ? RRF_OK : hip_fail(he);
   }
-  // Grid limits of the tiled kernels (64 x 64 output tiles).
+  // (The launches themselves put all output tiles, of at least 64 x 64 values,
+  // in grid.x: more than 2^24 of them would not fit the memory.)
   if (ceil_div(n, 64) > 65535 || ceil_div(r_old, 64) > 65535) return RRF_ERR_SHAPE;
   const int nsplit = map_splits(r_new, r_old, m, plan->num_cus);
   const size_t celems = (size_t)map_c_elems(r_new, r_old);

@@ -150,7 +150,6 @@ template hipError_t launch_fill_identity<double>(double*, int64_t, int64_t, int6
 template hipError_t launch_copy<float>(const float*, int64_t, float*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_copy<double>(const double*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t launch_convert<double, float>(const double*, int64_t, float*, int64_t, int64_t, int64_t, hipStream_t);
-template hipError_t launch_convert<float, double>(const float*, int64_t, double*, int64_t, int64_t, int64_t, hipStream_t);
 
 template <typename T>
 hipError_t launch_reflector_in(const T* V, int64_t ldv, const T* Tm, int64_t ldt, int64_t m,

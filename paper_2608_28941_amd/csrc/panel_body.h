@@ -1,6 +1,5 @@
 // Panel Householder QR with T factor (Alg. 2, geqrt step): the body of one
-// workgroup w of the panel grid (panel_kernel, and the panel part
-// of the look-ahead kernel).
+// workgroup w of the panel grid (panel_kernel).
 //
 // Factors the sampled panel Y (m x b, b <= 64) column by column with LAPACK
 // dlarfg / geqr2 semantics and builds the compact WY factor T (Eq. (4)) on the

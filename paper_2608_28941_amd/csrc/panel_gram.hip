@@ -12,7 +12,7 @@ __global__ __launch_bounds__(256) void panel_gram_kernel(GramPanelArgs ga) {
   panel_gram_body<BP, RT>(L, ga, (int)blockIdx.x);
 }
 
-// Row tiles per wavefront: the panel's registers (2 RT BP of the 512) leave
+// Row tiles per wavefront: the panel's registers (RT BP / 2 of the 512) leave
 // room for everything else up to RT BP = 512.
 constexpr int kGramRegs = 512;
 

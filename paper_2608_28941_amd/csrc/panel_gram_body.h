@@ -49,10 +49,12 @@
 // What bounds it: the exchanges (about 5 us each at 64 workgroups) and the
 // serial 16-column factorisations (5 us each, about 650 cycles a column: one
 // chain of a reciprocal square root, a reciprocal and lane broadcasts).
-// Measured (rrf_panel_qr, the whole call): 16384 x 64 109 us, against 409 us
-// for the column-by-column grid that 64-column panels took before; 4096 x 32
-// 65 us against 85 for the recurrence on all of F with two workgroup barriers
-// per column (1.3 us a column).  In the look-ahead launch at 4096 x 4096 fp32,
+// Measured (rrf_panel_qr with this panel, the whole call): 16384 x 64 of
+// condition 1e2, six sweeps, 173 us, against 409 us for the column-by-column
+// grid (which that call takes by default: V here is two to three times as far
+// from the exact one; a run's Q and B do not show it); 3000 x 32 of
+// condition 1e2 89 us against 115 for the recurrence on all of F with two
+// workgroup barriers per column.  In the look-ahead launch at 4096 x 4096 fp32,
 // b = 32: 58 -> 35 us per block.
 //
 // The body runs as a kernel of its own (panel_gram.hip) or on the first

@@ -231,8 +231,8 @@ constexpr int64_t kGramSlots = 10 * 256;
 constexpr int64_t kGramPartWords = 2LL * kMaxGramWGs * kGramSlots * 2;
 constexpr int64_t kGramSumWords = 2LL * kGramSlots * 2;
 // Columns x row tiles of a Gram panel inside the update's launch: its
-// registers (twice that) beside the rest of the body must leave two
-// workgroups per compute unit.
+// registers (half that: 128 of the 256 that two workgroups per compute unit
+// leave) go beside the rest of the body.
 constexpr int kGramFusedRegs = 256;
 struct GramPanelArgs {
   PanelArgs p;                 // Y, ldy, m, b, V, Tm, tau, st, G, epoch_base
