@@ -106,19 +106,17 @@ SCALED = [
 @pytest.mark.parametrize("name,m,n,b,tol", SCALED)
 def test_scaled_workloads(name, m, n, b, tol):
     # Element by element, in the default configuration: the look-ahead with
-    # the Gram panel inside the update's launch (blocks of b > 32 columns of
-    # these small matrices run as 32-column sub-blocks).
+    # the Gram panel inside the update's launch, sub-blocks of up to 64 columns.
     w = W.scaled(name, m, n, block_b=b, tol=tol)
     _check_against_live_oracle(w, W.build_matrix(w), elementwise=True)
 
 
 @pytest.mark.parametrize("name,m,n,b,tol", [SCALED[1], SCALED[2], SCALED[5]])
-def test_scaled_workloads_64_column_subblocks(monkeypatch, name, m, n, b, tol):
-    # Element by element with 64-column sub-blocks (the width large matrices
-    # take, e.g. 16384 x 16384): the column-by-column look-ahead path
-    # (update_panel_kernel with its fused sample, the redundant panel update
-    # in thin_apply_kernel, block 0's panel beside the first sample).
-    monkeypatch.setenv("RRF_SUBBLOCK", "64")
+def test_scaled_workloads_32_column_subblocks(monkeypatch, name, m, n, b, tol):
+    # Element by element with blocks of 48 and 64 columns as 32-column
+    # sub-blocks (the look-ahead at that width, its redundant panel update in
+    # thin_apply_kernel<2>, block 0's panel beside the first sample).
+    monkeypatch.setenv("RRF_SUBBLOCK", "32")
     w = W.scaled(name, m, n, block_b=b, tol=tol)
     _check_against_live_oracle(w, W.build_matrix(w), elementwise=True)
 
@@ -134,9 +132,9 @@ def test_scaled_workloads_tsqr_panel(monkeypatch, name, m, n, b, tol):
 @pytest.mark.parametrize("name,m,n,b,tol", [SCALED[0], SCALED[1], SCALED[2], SCALED[3],
                                             SCALED[4], SCALED[5]])
 def test_scaled_workloads_without_lookahead(monkeypatch, name, m, n, b, tol):
-    # Same bar with the look-ahead off (every panel in its own launch, no
-    # redundant panel update, no block-0 sample/panel launch; b <= 32: the
-    # Gram panel, queued during the stop test).
+    # Same bar with the look-ahead off (every panel in its own launch, queued
+    # during the stop test, no redundant panel update, no block-0 sample/panel
+    # launch).
     monkeypatch.setenv("RRF_LOOKAHEAD", "0")
     w = W.scaled(name, m, n, block_b=b, tol=tol)
     _check_against_live_oracle(w, W.build_matrix(w), elementwise=True)
@@ -144,7 +142,8 @@ def test_scaled_workloads_without_lookahead(monkeypatch, name, m, n, b, tol):
 
 @pytest.mark.parametrize("name,m,n,b,tol", SCALED)
 def test_scaled_workloads_gram_panel(monkeypatch, name, m, n, b, tol):
-    # Same bar with the Gram-matrix panel (chosen at plan creation).
+    # Same bar with the Gram-matrix panel forced (chosen at plan creation):
+    # every block a sub-block of its own.
     monkeypatch.setenv("RRF_PANEL", "gram")
     w = W.scaled(name, m, n, block_b=b, tol=tol)
     _check_against_live_oracle(w, W.build_matrix(w))
@@ -225,31 +224,32 @@ def test_subtract_mode_matches_oracle():
 
 @pytest.mark.parametrize("lookahead", ["1", "0"])
 def test_lookahead_tall_panel_elementwise(monkeypatch, lookahead):
-    # 12288 rows at b = 64: the panel inside the look-ahead launch holds 64
-    # rows per thread (panels above 8192 rows); k = 320 in five blocks,
-    # E / sigma^2 = 3.0 at k = 256 and 0.17 at 320.
+    # 12288 rows at b = 64: within 64 workgroups the panel inside the
+    # look-ahead launch holds four row tiles per wavefront, the most its
+    # registers allow; k = 320 in five blocks, E / sigma^2 = 3.0 at k = 256 and
+    # 0.17 at 320.
     monkeypatch.setenv("RRF_LOOKAHEAD", lookahead)
-    monkeypatch.setenv("RRF_SUBBLOCK", "64")
+    monkeypatch.setenv("RRF_LA_GRAM_WGS", "64")
     w = W.scaled("square_fp64_16384", 12288, 384, block_b=64, tol=1e-2)
     _, _, k, _ = _check_against_live_oracle(w, W.build_matrix(w), elementwise=True)
     assert k == 320
 
 
 @pytest.mark.parametrize("name,m,n,b,tol,wgs", [
-    ("galore_fp32_4096x4096", 1024, 1024, 32, None, 64),   # 4 rows per thread, 32 workgroups
-    ("galore_fp32_4096x4096", 1024, 1024, 32, None, 16),   # 8 rows per thread
-    ("galore_fp32_4096x4096", 1024, 1024, 32, None, 8),    # 16 rows per thread
-    ("tall_fp64_131072x2048", 8192, 256, None, None, 64),  # 16 rows per thread, 64 workgroups
-    ("tiny_fp64_500x300", 500, 300, 16, 1e-4, 64),         # 16 columns, 4 rows per thread
-    ("tiny_fp64_500x300", 500, 300, 16, 1e-4, 4),          # 8 rows per thread
-    ("tiny_fp64_500x300", 500, 300, 16, 1e-4, 2),          # 16 rows per thread
+    ("galore_fp32_4096x4096", 1024, 1024, 32, None, 64),   # 1 row tile per wavefront, 16 workgroups
+    ("galore_fp32_4096x4096", 1024, 1024, 32, None, 16),   # the same, the most workgroups
+    ("galore_fp32_4096x4096", 1024, 1024, 32, None, 8),    # 2 row tiles
+    ("tall_fp64_131072x2048", 8192, 256, None, None, 64),  # 2 row tiles, 64 workgroups
+    ("tiny_fp64_500x300", 500, 300, 16, 1e-4, 64),         # 2 blocks of 16 columns
+    ("tiny_fp64_500x300", 500, 300, 16, 1e-4, 4),          # 2 row tiles
+    ("tiny_fp64_500x300", 500, 300, 16, 1e-4, 2),          # 4 row tiles
     ("tiny_fp64_500x300", 333, 250, 20, 1e-5, 64),         # 20 of 32 columns, ragged
 ])
 def test_lookahead_gram_panel_shapes(monkeypatch, name, m, n, b, tol, wgs):
-    # Blocks of at most 32 columns: the next block's Gram panel runs on the
-    # first workgroups of the update's launch; RRF_LA_GRAM_WGS caps its grid,
-    # which picks the rows per thread.  Element by element against the
-    # oracle.
+    # The next sub-block's Gram panel runs on the first workgroups of the
+    # update's launch; RRF_LA_GRAM_WGS caps its grid, which picks the row tiles
+    # per wavefront (one workgroup holds up to four at 32 columns).  Element by
+    # element against the oracle.
     monkeypatch.setenv("RRF_LA_GRAM_WGS", str(wgs))
     w = W.scaled(name, m, n, block_b=b, tol=tol)
     _check_against_live_oracle(w, W.build_matrix(w), elementwise=True)
@@ -267,16 +267,15 @@ def test_deterministic_repeat_lookahead_gram():
         assert torch.equal(Q1, Q2) and torch.equal(B1, B2)
 
 
-@pytest.mark.parametrize("sub", ["64", "auto"])
+@pytest.mark.parametrize("sub", ["32", "auto"])
 @pytest.mark.parametrize("name,m,n,b,tol", [
     ("square_fp64_16384", 2048, 2048, 128, 1e-5),    # two 64-column sub-blocks
     ("tiny_fp64_500x300", 333, 250, 100, 1e-5),      # sub-blocks of 64 and 36
-    ("galore_fp32_4096x4096", 1024, 1024, 80, 2e-2), # 64 and 16: mixed panel routes
+    ("galore_fp32_4096x4096", 1024, 1024, 80, 2e-2), # 64 and 16: no look-ahead
 ])
 def test_blocks_wider_than_64(monkeypatch, name, m, n, b, tol, sub):
-    # block_b > 64 runs as sub-blocks of at most 64 columns (32 for these
-    # small matrices by default) with the stop test at block ends; the oracle
-    # factors each block whole.
+    # block_b > 64 runs as sub-blocks of at most 64 columns (RRF_SUBBLOCK: 32)
+    # with the stop test at block ends; the oracle factors each block whole.
     if sub != "auto":
         monkeypatch.setenv("RRF_SUBBLOCK", sub)
     w = W.scaled(name, m, n, block_b=b, tol=tol)
@@ -284,32 +283,38 @@ def test_blocks_wider_than_64(monkeypatch, name, m, n, b, tol, sub):
     assert k % b == 0 or k == min(m, n)
 
 
-def test_panel_beyond_register_capacity():
-    # 131072 rows at b = 64: no register-resident panel grid holds the panel,
-    # so it takes the tall-skinny QR tree.  Fixed rank k = 128 (tol = 0,
-    # k_cap = n); the oracle is the plain definition of the result
+@pytest.mark.parametrize("b,updates", [(64, 2), (32, 4)])
+def test_panel_beyond_register_capacity(b, updates):
+    # 140000 rows: no register-resident panel grid holds 64 columns, so blocks
+    # of 64 take the tall-skinny QR tree, and blocks of 32 stay one to a
+    # sub-block (its scratch is of the plan's own width).  Fixed rank k = 128
+    # (tol = 0, k_cap = n); the oracle is the plain definition of the result
     # (Theorem 3.1): the Householder QR of A Omega_k (the oracle's geqr2 and
     # org2r) and B = Q^T A.
-    w = W.scaled("tall_fp64_131072x2048", 131072, 128, block_b=64, tol=0.0)
+    m = 140000
+    w = W.scaled("tall_fp64_131072x2048", m, 128, block_b=b, tol=0.0)
     A = W.build_matrix(w)
-    say("tall 131072x128 b=64: oracle plain definition")
-    Om = oracle.normal_v1(w.sketch_seed, 128, 0, 128, dtype=np.float64)
-    Vo, tauo = oracle.geqr2(A @ Om)
-    Qo = oracle.org2r(Vo, tauo)
-    Bo = Qo.T @ A
-    say("tall 131072x128 b=64: rrf_run")
-    Q, B, k, _, st = _run(A, w)
-    assert k == 128 and st == rrf.RRF_OK
+    if m not in _ORACLE:
+        say("tall 140000x128: oracle plain definition")
+        Om = oracle.normal_v1(w.sketch_seed, 128, 0, 128, dtype=np.float64)
+        Vo, tauo = oracle.geqr2(A @ Om)
+        Qo = oracle.org2r(Vo, tauo)
+        _ORACLE[m] = Qo, Qo.T @ A
+    Qo, Bo = _ORACLE[m]
+    say(f"tall 140000x128 b={b}: rrf_run")
+    with rrf.Plan(torch.float64, m, 128, b) as p:
+        Q, B, k = p.run(to_dev(A), 0.0, b, w.sketch_seed)
+        st, launches = p.last_status, p.stage_stats()["update"]["launches"]
+        Q, B = to_host(Q), to_host(B)
+    assert k == 128 and st == rrf.RRF_OK and launches == updates
     tq, tb = _elementwise_bound(A, k, w)
     assert np.max(np.abs(Q - Qo)) <= tq
     assert np.max(np.abs(B - Bo)) <= tb
     assert orth_err(Q) <= ORTH_TOL[np.dtype(np.float64)]
 
 
-def test_deterministic_repeat_lookahead(monkeypatch):
-    # Bit-identical results from two runs of the look-ahead path (b = 64,
-    # 64-column sub-blocks).
-    monkeypatch.setenv("RRF_SUBBLOCK", "64")
+def test_deterministic_repeat_lookahead():
+    # Bit-identical results from two runs of the look-ahead path (b = 64).
     w = W.scaled("square_fp64_16384", 2048, 2048, tol=1e-5)
     A = to_dev(W.build_matrix(w))
     with rrf.Plan(torch.float64, 2048, 2048, 64) as p:
